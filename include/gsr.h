@@ -105,10 +105,10 @@ typedef struct gsr_options {
                              component); 2 = as 1 after DPP sums over lane quads; 3 = as 1 after
                              DPP sums over 16-lane rows, one LDS atomic instruction per entry;
                              4 = as 3 with a reduce-scatter over the rows */
-  int32_t project_table;  /* projection's tile counting: 0 = per-wavefront grouping of lanes that
-                             share a tile, then device atomics; 1 = a per-workgroup table of tiles
-                             in LDS, one device atomic per (workgroup, tile) (pays where wide
-                             footprints make the device atomics' throughput the limit) */
+  int32_t project_table;  /* projection's tile counting: a workgroup counts its records into a table of
+                             tiles in LDS, then takes one device atomic per tile; with 0 the workgroups
+                             whose means lie far apart on the tile grid count with device atomics
+                             directly, with 1 none does */
   float near_plane, far_plane;
   float eps2d;           /* low-pass dilation of the 2D covariance */
   float sigma_extent;    /* footprint radius in standard deviations */

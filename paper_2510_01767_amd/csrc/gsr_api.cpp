@@ -312,6 +312,14 @@ int n_cus(gsr_plan *p) {
   return p->n_cus;
 }
 
+// The view table of a step on these cameras.
+ViewTable step_table(const gsr_plan &p, const gsr_camera *cams) {
+  ViewTable t = view_table(p);
+  t.cams = cams;
+  t.opts = kopts(p);
+  return t;
+}
+
 gsr_status zero_grads(gsr_plan *plan, const gsr_grads *g, void *stream) {
   const int64_t n = plan->prob.n;
   const int K = (plan->prob.sh_degree + 1) * (plan->prob.sh_degree + 1);
@@ -329,7 +337,7 @@ gsr_status zero_grads(gsr_plan *plan, const gsr_grads *g, void *stream) {
 gsr_status enqueue_front(gsr_plan *plan, const gsr_gaussians *g, const gsr_camera *cams, const KWs &ws,
                          void *stream, bool plain_raster_fwd, float *images, float *depth = nullptr,
                          uint32_t *pair_counts = nullptr) {
-  const ViewTable tbl = view_table(*plan);
+  const ViewTable tbl = step_table(*plan, cams);
   const KParams kp = kparams(*plan, g);
   const KOpts ko = kopts(*plan);
   const int V = plan->prob.n_views;
@@ -386,7 +394,7 @@ gsr_status enqueue_batched_l1(gsr_plan *plan, const gsr_gaussians *g, const gsr_
 gsr_status enqueue_plain_l1(gsr_plan *plan, const gsr_gaussians *g, const gsr_camera *cams, const float *targets,
                             float *images, float *loss, const gsr_grads *grads, const gsr_stats *stats,
                             const KWs &ws, void *stream) {
-  const ViewTable tbl = view_table(*plan);
+  const ViewTable tbl = step_table(*plan, cams);
   const KParams kp = kparams(*plan, g);
   const KOpts ko = kopts(*plan);
   const int V = plan->prob.n_views;
@@ -700,7 +708,7 @@ gsr_status gsr_visibility_mask(gsr_plan *plan, const gsr_gaussians *g, const gsr
   const KWs k = ws_view(*plan, ws);
   const float box[6] = {aabb ? aabb[0] : 0.f, aabb ? aabb[1] : 0.f, aabb ? aabb[2] : 0.f,
                         aabb ? aabb[3] : 0.f, aabb ? aabb[4] : 0.f, aabb ? aabb[5] : 0.f};
-  STAGE(launch_setup(view_table(*plan), k, 0, 0, 0, plan->prob.n, stream), "setup");
+  STAGE(launch_setup(step_table(*plan, cams), k, 0, 0, 0, plan->prob.n, stream), "setup");
   STAGE(launch_visibility(kparams(*plan, g), cams, kopts(*plan), k, box, view_bits, keep_out, in_block, stream),
          "visibility");
   return GSR_OK;

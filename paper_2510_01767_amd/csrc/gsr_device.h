@@ -14,16 +14,6 @@ namespace gsr {
 
 // ------------------------------------------------------------ camera, geometry
 
-// One view's camera in float64, with the per-view constants of the
-// projection computed once per workgroup (kept in LDS).
-struct Cam64 {
-  double R[9], t[3], fx, fy, cx, cy;
-  double limx, limy;  // clamp of x/z and y/z inside the Jacobian
-  double itw, ith;    // 1 / tile size (powers of two, so x * itw == x / tile_w)
-  double cc[3];       // R^T t: mean + cc is the mean relative to the camera centre
-  int W, H, tiles_x, tiles_y;
-};
-
 __device__ __forceinline__ Cam64 cam64(const gsr_camera &c, const ViewInfo &vi, const KOpts &o) {
   Cam64 k;
 #pragma unroll
@@ -38,14 +28,30 @@ __device__ __forceinline__ Cam64 cam64(const gsr_camera &c, const ViewInfo &vi, 
   k.H = vi.H;
   k.tiles_x = vi.tiles_x;
   k.tiles_y = vi.tiles_y;
+  k.tile_base = (int32_t)vi.tile_base;
+  k.pad = 0;
   k.limx = (double)o.jac_clamp * (0.5 * k.W / k.fx);
   k.limy = (double)o.jac_clamp * (0.5 * k.H / k.fy);
   k.itw = 1.0 / (double)o.tile_w;
   k.ith = 1.0 / (double)o.tile_h;
 #pragma unroll
   for (int a = 0; a < 3; a++) k.cc[a] = k.R[a] * k.t[0] + k.R[3 + a] * k.t[1] + k.R[6 + a] * k.t[2];
+  k.tiles_w = (double)k.tiles_x * (double)o.tile_w;
+  k.tiles_h = (double)k.tiles_y * (double)o.tile_h;
+  // lambda_max(J W Sigma W^T J^T + eps) <= |J|_F^2 max(s)^2 + eps, with |J|_F
+  // at its clamped limits, and sqrt(x + y) <= sqrt(x) + sqrt(y); the radius is
+  // rounded up (one pixel) and two more cover the rounding of all of it
+  k.reach_s = (double)o.sigma * sqrt(k.fx * k.fx * (1.0 + k.limx * k.limx) + k.fy * k.fy * (1.0 + k.limy * k.limy));
+  k.reach_z = (double)o.sigma * sqrt((double)o.eps2d) + 3.0;
   return k;
 }
+
+// The cameras that the set-up kernel left in the workspace, read through the
+// scalar cache where the view is the same for the whole wavefront: the
+// constants then sit in scalar registers instead of LDS reads and vector
+// registers.
+using CamPtr = const __attribute__((address_space(4))) Cam64 *;
+__device__ __forceinline__ CamPtr cam_ptr(const KWs &ws) { return (CamPtr)(uintptr_t)ws.hdr->cams; }
 
 // The cameras of views [0, n_views) into LDS (one per thread, then a barrier).
 __device__ __forceinline__ void load_cams(Cam64 *s_cam, const gsr_camera *cams, const ViewInfo *views, int n_views,
@@ -114,13 +120,13 @@ struct GeoF {
   double mu[3];
   double Sig[6];
   double opac;
-  double smax2;  // largest eigenvalue of Sigma = max scale^2
+  double smax;  // largest scale
 };
 
 __device__ __forceinline__ void load_geo_fwd(const KParams &p, int64_t i, GeoF &g) {
   double s[3], q[4], qn, Rq[9];
   geo_core(p, i, g.mu, s, q, qn, Rq, g.Sig, g.opac);
-  g.smax2 = fmax(fmax(s[0] * s[0], s[1] * s[1]), s[2] * s[2]);
+  g.smax = fmax(fmax(s[0], s[1]), s[2]);
 }
 
 __device__ __forceinline__ double sig_at(const double S[6], int r, int c) {
@@ -141,32 +147,41 @@ struct Proj {
   int x0, y0, x1, y1;   // inclusive tile rectangle
 };
 
-// Returns true when the Gaussian is visible (depth inside (near, far),
-// positive-definite 2D covariance, non-empty tile rectangle).
-// Cheap conservative test: false only when the Gaussian is certainly not
-// visible.  lambda_max(J W Sigma W^T J^T) <= |J|_F^2 max(s)^2, so the exact
-// tile rectangle lies inside the one built from this bound.
-__device__ __forceinline__ bool maybe_visible(const GeoF &g, const Cam64 &k, const KOpts &o) {
+// Cheap test of one Gaussian against one view: kOut when it is certainly not
+// visible, kIn when it certainly is, kMaybe where the exact test (project_view)
+// decides.  The exact tile rectangle lies inside the one built from the
+// footprint bound of cam64, and is not empty when the mean lies a pixel or
+// more inside the grid.  Both sides of the comparisons are multiplied by z, so
+// there is no division and no square root.  kIn also needs the 2D covariance
+// to be certainly positive definite in float64: a dilation of 0.01 or more
+// under a footprint of at most 1e4 pixels (its determinant then exceeds its
+// rounding by 1e5), and `sane` parameters.  An infinite or undefined bound
+// leaves the decision to the exact test.
+enum Cull { kOut, kMaybe, kIn };
+
+template <bool ACCEPT, class C>
+__device__ __forceinline__ Cull cull_view(const double mu[3], double smax, bool sane, const C &k, const KOpts &o) {
   double tc[3];
 #pragma unroll
-  for (int r = 0; r < 3; r++)
-    tc[r] = k.R[r * 3 + 0] * g.mu[0] + k.R[r * 3 + 1] * g.mu[1] + k.R[r * 3 + 2] * g.mu[2] + k.t[r];
+  for (int r = 0; r < 3; r++) tc[r] = k.R[r * 3 + 0] * mu[0] + k.R[r * 3 + 1] * mu[1] + k.R[r * 3 + 2] * mu[2] + k.t[r];
   const double tz = tc[2];
-  if (!(tz > (double)o.near_plane && tz < (double)o.far_plane)) return false;
-  const double iz = 1.0 / tz;
-  const double ux = tc[0] * iz, uy = tc[1] * iz;
-  const double mx = k.fx * ux + k.cx, my = k.fy * uy + k.cy;
-  const double u = fmin(fabs(ux), k.limx), v = fmin(fabs(uy), k.limy);
-  const double jn2 = (k.fx * iz) * (k.fx * iz) * (1.0 + u * u) + (k.fy * iz) * (k.fy * iz) * (1.0 + v * v);
-  const double rb = ceil((double)o.sigma * sqrt(jn2 * g.smax2 + (double)o.eps2d)) + 1.0;
-  return !(floor((mx + rb) * k.itw) < 0.0 || floor((my + rb) * k.ith) < 0.0 ||
-           floor((mx - rb) * k.itw) > k.tiles_x - 1 || floor((my - rb) * k.ith) > k.tiles_y - 1);
+  if (!(tz > (double)o.near_plane && tz < (double)o.far_plane)) return kOut;
+  const double ax = __fma_rn(k.fx, tc[0], k.cx * tz), ay = __fma_rn(k.fy, tc[1], k.cy * tz);
+  const double wz = k.tiles_w * tz, hz = k.tiles_h * tz, rs = k.reach_s * smax;
+  const double rz = __fma_rn(k.reach_z, tz, rs);
+  // (short circuits: a wavefront's neighbours in storage mostly leave at the same test)
+  if (ax + rz < 0.0 || ay + rz < 0.0 || ax - rz > wz || ay - rz > hz) return kOut;
+  if (ACCEPT && sane && o.eps2d >= 0.01f && rs <= 1.0e4 * tz && ax >= tz && ay >= tz && ax <= wz - tz && ay <= hz - tz)
+    return kIn;
+  return kMaybe;
 }
 
+// Returns true when the Gaussian is visible (depth inside (near, far),
+// positive-definite 2D covariance, non-empty tile rectangle).
 // RECT = false (the reverse pass, on pairs known to be visible) stops after
 // the conic: no eigenvalue, radius or tile rectangle.
-template <bool RECT = true, class G>
-__device__ __forceinline__ bool project_view(const G &g, const Cam64 &k, const KOpts &o, Proj &P) {
+template <bool RECT = true, class G, class C>
+__device__ __forceinline__ bool project_view(const G &g, const C &k, const KOpts &o, Proj &P) {
 #pragma unroll
   for (int r = 0; r < 3; r++)
     P.tc[r] = k.R[r * 3 + 0] * g.mu[0] + k.R[r * 3 + 1] * g.mu[1] + k.R[r * 3 + 2] * g.mu[2] + k.t[r];

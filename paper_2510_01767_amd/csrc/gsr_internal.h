@@ -18,10 +18,38 @@ struct ViewInfo {
   int32_t pad[3];
 };
 
+// Rasterizer constants as kernel arguments.
+struct KOpts {
+  float near_plane, far_plane, eps2d, sigma, jac_clamp, alpha_min, alpha_max, T_min;
+  float bg[3];
+  float stat_scale;
+  int32_t tile_w, tile_h;
+  int32_t check_finite;
+  int32_t accumulate;
+};
+
+// The views of a step, with the cameras and constants the set-up kernel makes
+// the workspace's Cam64 from.
 struct ViewTable {
   ViewInfo v[GSR_MAX_VIEWS];
   int32_t n_views;
   int32_t pad[3];
+  const gsr_camera *cams;
+  KOpts opts;
+};
+
+// One view's camera in float64, with the per-view constants of the
+// projection and of the cull (cull_visible); made by the set-up kernel.
+struct Cam64 {
+  double R[9], t[3], fx, fy, cx, cy;
+  double limx, limy;  // clamp of x/z and y/z inside the Jacobian
+  double itw, ith;    // 1 / tile size (powers of two, so x * itw == x / tile_w)
+  double cc[3];       // R^T t: mean + cc is the mean relative to the camera centre
+  double tiles_w, tiles_h;  // the tile grid in pixels
+  double reach_s, reach_z;  // footprint bound reach_s max(scale) / z + reach_z pixels
+  int32_t W, H, tiles_x, tiles_y;
+  int32_t tile_base;  // (fewer than 2^25 tiles in all)
+  int32_t pad;
 };
 
 // Device-side header at the start of the workspace.
@@ -47,18 +75,9 @@ struct WsHeader {
   uint32_t queue[8][32];
   // per-view loss sums (scaled), added up in view order for the loss
   double view_loss[GSR_MAX_VIEWS];
+  Cam64 cams[GSR_MAX_VIEWS];
 };
 constexpr int kOrderBins = 1024;
-
-// Rasterizer constants as kernel arguments.
-struct KOpts {
-  float near_plane, far_plane, eps2d, sigma, jac_clamp, alpha_min, alpha_max, T_min;
-  float bg[3];
-  float stat_scale;
-  int32_t tile_w, tile_h;
-  int32_t check_finite;
-  int32_t accumulate;
-};
 
 struct KParams {
   const float *means, *log_scales, *quats, *logits, *sh;

@@ -27,7 +27,10 @@ namespace gsr {
 __global__ void k_setup(ViewTable table, KWs ws, int64_t zlo, int64_t zcount, int zero_bits, int64_t n) {
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  if (gid < table.n_views) ws.views[gid] = table.v[gid];
+  if (gid < table.n_views) {
+    ws.views[gid] = table.v[gid];
+    ws.hdr->cams[gid] = cam64(table.cams[gid], table.v[gid], table.opts);
+  }
   if (gid == 0) {
     WsHeader *h = ws.hdr;
     h->overflow = 0;
@@ -98,23 +101,32 @@ __device__ __forceinline__ void wave_expand(uint32_t count, F f) {
   }
 }
 
-// With TABLE, a workgroup's table of the tiles its records touch, in LDS:
-// open addressing on the tile id, linear probing.  cnt counts the ranked
-// entries (the LDS atomic's return value is the rank within the workgroup),
-// fill the overflow ones; base receives the workgroup's start in the tile's
-// bucket.
-constexpr int kTileTable = 1024, kTileProbes = 16;
+// A workgroup's table of the tiles its records touch, in LDS: open addressing
+// on the tile id, linear probing.  cnt counts the ranked entries (the LDS
+// atomic's return value is the rank within the workgroup), fill the overflow
+// ones; base receives the workgroup's start in the tile's bucket.
+//
+// Sizes, measured on six workloads (k_project in us: one full-HD view of 1 M
+// Gaussians, four 1600 x 900 views of 1.5 M, the 16-view block of 3 M, camera
+// selection over 8 views of 1 M, the 32-view city of 8 M, the 2160p cloud of
+// 20 M).  Sixteen probes cost more than the atomics they save where the
+// table is full: 512 tiles and 16 probes 72, 76, 675, 169, 2211, 7400; 4
+// probes 51, 63, 644, 158, 2158, 7325; 4 probes and no insertion for
+// footprints of more than 16 tiles 49, 63, 647, 152, 2190, 6731; with 1024
+// tiles 50, 65, 659, 164, 2143, 6971.  Grouping the lanes of a wavefront that
+// share a tile by ballots instead of the table: 50, 91, 1168, 285, 3693, 19327.
+constexpr int kTileTable = 512, kTileProbes = 4;
+constexpr uint32_t kTableOver = 12u;  // tiles past the fourth
 constexpr uint32_t kNoTile = 0xffffffffu;
 
-template <int N>
 struct TileTable {
-  uint32_t key[N], cnt[N], fill[N], base[N];
+  uint32_t key[kTileTable], cnt[kTileTable], fill[kTileTable], base[kTileTable];
 };
 
 // The table slot of tile t, inserting it if absent; -1 when the probe
 // sequence is full.
-__device__ __forceinline__ int tile_table_slot(TileTable<kTileTable> &tt, uint32_t t) {
-  const uint32_t h = (t * 2654435761u) >> 22;  // 10 bits
+__device__ __forceinline__ int tile_table_slot(TileTable &tt, uint32_t t) {
+  const uint32_t h = (t * 2654435761u) >> 23;  // 9 bits
   for (int k = 0; k < kTileProbes; k++) {
     const int e = (int)((h + (uint32_t)k) & (uint32_t)(kTileTable - 1));
     const uint32_t cur = *reinterpret_cast<volatile uint32_t *>(&tt.key[e]);
@@ -127,21 +139,42 @@ __device__ __forceinline__ int tile_table_slot(TileTable<kTileTable> &tt, uint32
   return -1;
 }
 
-template <int D, bool TABLE>
-__global__ __launch_bounds__(kBlock) void k_project(KParams p, const gsr_camera *cams, KOpts o, KWs ws,
-                                                    int view_lo, int view_hi, int or_bits) {
+// OR over the lanes of a wavefront, the same in every lane.
+__device__ __forceinline__ uint32_t wave_or(uint32_t x) {
+#pragma unroll
+  for (int m = 1; m < 64; m <<= 1) x |= (uint32_t)__shfl_xor((int)x, m);
+  return x;
+}
+
+// Smallest value over the wavefront, the same in every lane.
+__device__ __forceinline__ int wave_min(int x) {
+  x = min(x, __builtin_amdgcn_update_dpp(x, x, 0xB1, 0xf, 0xf, false));   // quad_perm [1,0,3,2]
+  x = min(x, __builtin_amdgcn_update_dpp(x, x, 0x4E, 0xf, 0xf, false));   // quad_perm [2,3,0,1]
+  x = min(x, __builtin_amdgcn_update_dpp(x, x, 0x141, 0xf, 0xf, false));  // row_half_mirror
+  x = min(x, __builtin_amdgcn_update_dpp(x, x, 0x140, 0xf, 0xf, false));  // row_mirror
+  x = min(x, __builtin_amdgcn_update_dpp(x, x, 0x142, 0xa, 0xf, false));  // row_bcast:15 into rows 1 and 3
+  x = min(x, __builtin_amdgcn_update_dpp(x, x, 0x143, 0xc, 0xf, false));  // row_bcast:31 into rows 2 and 3
+  return __builtin_amdgcn_readlane(x, 63);
+}
+
+// One thread per Gaussian, its visible views one after another.  Bound by the
+// rank atomics and the latency of the float64 chain (four wavefronts per
+// SIMD), not by bytes or instructions: without the atomics the 16-view block
+// took 0.61 of its 1.17 ms when they were grouped per wavefront (7.9 M
+// requests), 0.65 ms is what the workgroup table leaves.
+template <int D>
+__global__ __launch_bounds__(kBlock) void k_project(KParams p, KOpts o, KWs ws, int view_lo, int view_hi,
+                                                    int or_bits, int always) {
   constexpr int K = (D + 1) * (D + 1);
-  __shared__ Cam64 s_cam[GSR_MAX_VIEWS];
-  __shared__ ViewInfo s_view[GSR_MAX_VIEWS];
-  __shared__ TileTable<TABLE ? kTileTable : 1> s_tt;
-  for (int v = threadIdx.x; v < p.n_views; v += blockDim.x) s_view[v] = ws.views[v];
-  if (TABLE)
-    for (int e = threadIdx.x; e < kTileTable; e += blockDim.x) {
-      s_tt.key[e] = kNoTile;
-      s_tt.cnt[e] = 0u;
-      s_tt.fill[e] = 0u;
-    }
-  load_cams(s_cam, cams, ws.views, p.n_views, o);
+  __shared__ double s_cc[GSR_MAX_VIEWS][3];
+  __shared__ TileTable s_tt;
+  __shared__ uint32_t s_active;
+  __shared__ int s_span[4];  // smallest x, -x, y, -y over the workgroup's means, in tiles
+  const CamPtr cams = cam_ptr(ws);
+  for (int k = threadIdx.x; k < 3 * p.n_views; k += blockDim.x) s_cc[k / 3][k % 3] = ws.hdr->cams[k / 3].cc[k % 3];
+  if (threadIdx.x == 0) s_active = 0u;
+  if (threadIdx.x < 4) s_span[threadIdx.x] = INT32_MAX;
+  __syncthreads();
   const int64_t n = p.n;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const bool valid = i < n;
@@ -161,15 +194,69 @@ __global__ __launch_bounds__(kBlock) void k_project(KParams p, const gsr_camera 
   uint32_t bits = (valid && or_bits) ? ws.view_bits[i] : 0u;
   uint32_t fresh = 0u;  // views found visible by this call
   const int lane = lane_id();
-  const uint64_t below = (1ull << lane) - 1ull;
-  for (int v = view_lo; v < view_hi; v++) {
-    const ViewInfo &vi = s_view[v];
-    const Cam64 &cam = s_cam[v];
+  // which views the cull leaves open, then only those that some lane of the
+  // workgroup has open: its lanes stay together in the loop over them
+  uint32_t open = 0u;
+  if (keep)
+    for (int v = view_lo; v < view_hi; v++)
+      open |= (cull_view<false>(g.mu, g.smax, false, cams[v], o) != kOut ? 1u : 0u) << v;
+  const uint32_t mine = wave_or(open);
+  uint32_t active = mine;
+  if (lane == 0 && active) atomicOr(&s_active, active);
+  __syncthreads();
+  active = s_active;
+  if (active) {
+    for (int e = threadIdx.x; e < kTileTable; e += blockDim.x) {
+      s_tt.key[e] = kNoTile;
+      s_tt.cnt[e] = 0u;
+      s_tt.fill[e] = 0u;
+    }
+    // how far the workgroup's means lie apart on the first active view's grid
+    if (!always) {
+      const auto &cam = cams[__builtin_amdgcn_readfirstlane(__builtin_ctz(active))];
+      int tx = 0, ty = 0;
+      bool seen = false;
+      if (keep) {
+        const float z = (float)(cam.R[6] * g.mu[0] + cam.R[7] * g.mu[1] + cam.R[8] * g.mu[2] + cam.t[2]);
+        const float x = (float)(cam.R[0] * g.mu[0] + cam.R[1] * g.mu[1] + cam.R[2] * g.mu[2] + cam.t[0]);
+        const float y = (float)(cam.R[3] * g.mu[0] + cam.R[4] * g.mu[1] + cam.R[5] * g.mu[2] + cam.t[1]);
+        seen = z > o.near_plane;
+        // (clamped to 2^20 tiles; a NaN counts as 0)
+        tx = (int)fminf(fmaxf((float)(cam.fx * cam.itw) * (x / z), -1048576.0f), 1048576.0f);
+        ty = (int)fminf(fmaxf((float)(cam.fy * cam.ith) * (y / z), -1048576.0f), 1048576.0f);
+      }
+      const int x0 = wave_min(seen ? tx : INT32_MAX), x1 = wave_min(seen ? -tx : INT32_MAX);
+      const int y0 = wave_min(seen ? ty : INT32_MAX), y1 = wave_min(seen ? -ty : INT32_MAX);
+      if (lane == 0) {
+        atomicMin(&s_span[0], x0);
+        atomicMin(&s_span[1], x1);
+        atomicMin(&s_span[2], y0);
+        atomicMin(&s_span[3], y1);
+      }
+    }
+  }
+  __syncthreads();
+  // The workgroup counts into its table first (the rank within the workgroup
+  // from the LDS atomic), then takes one device atomic per distinct tile for
+  // all of it; a tile the table cannot hold takes device atomics directly.
+  // Gaussians in no spatial order share few tiles: a workgroup whose means
+  // lie further apart than the table's size and half the view counts with
+  // device atomics alone, without barriers (32-view city in random order 4.1
+  // ms so, 5.4 with the table; in spatial order 2.2 with it, and with a line
+  // at 16 rows of tiles, which takes the workgroups across a jump of that
+  // order for disordered ones, 2.6).
+  bool direct = false;
+  if (!always && active) {
+    const auto &cam = cams[__builtin_amdgcn_readfirstlane(__builtin_ctz(active))];
+    const int64_t w = -(int64_t)s_span[1] - s_span[0], h = -(int64_t)s_span[3] - s_span[2];
+    direct = h * cam.tiles_x + w > max((int64_t)kTileTable, (int64_t)cam.tiles_x * cam.tiles_y / 2);
+    if (direct) active = mine;  // (no barriers below: each wavefront its own views)
+  }
+  for (active = (uint32_t)__builtin_amdgcn_readfirstlane((int)active); active; active &= active - 1u) {
+    const int v = __builtin_ctz(active);
+    const auto &cam = cams[v];
     Proj P;
-    // the exact projection only where the conservative bound leaves a chance
-    const bool vis = keep && maybe_visible(g, cam, o) && project_view(g, cam, o, P);
-    // (the whole wavefront, with TABLE the whole workgroup, stays in the loop)
-    if (TABLE ? !__syncthreads_or(vis) : __ballot(vis) == 0ull) continue;
+    const bool vis = ((open >> v) & 1u) && project_view(g, cam, o, P);
     const int64_t r = (int64_t)v * n + i;
     uint4 r3 = make_uint4(0u, 0u, 0u, 0u);
     int wx = 1, ntiles = 0;
@@ -194,10 +281,11 @@ __global__ __launch_bounds__(kBlock) void k_project(KParams p, const gsr_camera 
     // (row-major) the record's rank in the tile's bucket comes out of the
     // count, kept so that the scatter needs no atomics; further tiles (large
     // footprints) are counted apart and placed after the ranked ones.
-    const int x0 = P.x0, y0 = P.y0;
+    const int x0 = P.x0, y0 = P.y0, tiles_x = cam.tiles_x;
+    const int32_t tile_base = cam.tile_base;
     auto tile_q = [&](int q) -> int32_t {
       const int dy = q / wx, dx = q - dy * wx;
-      return (int32_t)(vi.tile_base + (int64_t)(y0 + dy) * vi.tiles_x + (x0 + dx));
+      return tile_base + (y0 + dy) * tiles_x + (x0 + dx);
     };
     // tile q of lane src's record (shuffles: every lane calls it)
     const int32_t t_first = vis ? tile_q(0) : 0;
@@ -205,36 +293,31 @@ __global__ __launch_bounds__(kBlock) void k_project(KParams p, const gsr_camera 
     auto tile_of = [&](int src, uint32_t q) -> int32_t {
       const int w = __shfl(wx, src), first = __shfl(t_first, src);
       const int dy = (int)(q / (uint32_t)w), dx = (int)q - dy * w;
-      return first + dy * vi.tiles_x + dx;
+      return first + dy * tiles_x + dx;
     };
     uint32_t rk[4];
-    if constexpr (TABLE) {
-      // The workgroup counts into its table first (the rank within the
-      // workgroup from the LDS atomic), then takes one device atomic per
-      // distinct tile for all of it; a tile the table cannot hold takes
-      // device atomics directly.  For wide footprints (many tiles per record,
-      // many records per tile) the device atomics' throughput is what limits
-      // this kernel, and the table divides their number.
-      int slot[4];
+    int slot[4];
 #pragma unroll
-      for (int q = 0; q < 4; q++) {
-        slot[q] = -1;
-        rk[q] = 0u;
-        if (q < ntiles) {
-          const int32_t t = tile_q(q);
-          slot[q] = tile_table_slot(s_tt, (uint32_t)t);
-          if (slot[q] >= 0) rk[q] = atomicAdd(&s_tt.cnt[slot[q]], 1u);
-          else rk[q] = atomicAdd(&ws.tile_count[t], 1u);
-        }
+    for (int q = 0; q < 4; q++) {
+      slot[q] = -1;
+      rk[q] = 0u;
+      if (q < ntiles) {
+        const int32_t t = tile_q(q);
+        slot[q] = direct ? -1 : tile_table_slot(s_tt, (uint32_t)t);
+        if (slot[q] >= 0) rk[q] = atomicAdd(&s_tt.cnt[slot[q]], 1u);
+        else rk[q] = atomicAdd(&ws.tile_count[t], 1u);
       }
-      wave_expand(over, [&](int src, uint32_t k, bool live) {
-        const int32_t t = tile_of(src, k + 4u);
-        if (live) {
-          const int e = tile_table_slot(s_tt, (uint32_t)t);
-          if (e >= 0) atomicAdd(&s_tt.fill[e], 1u);
-          else atomicAdd(&ws.tile_fill[t], 1u);
-        }
-      });
+    }
+    wave_expand(over, [&](int src, uint32_t k, bool live) {
+      const int32_t t = tile_of(src, k + 4u);
+      const bool wide = direct || (uint32_t)__shfl((int)over, src) > kTableOver;
+      if (live) {
+        const int e = wide ? -1 : tile_table_slot(s_tt, (uint32_t)t);
+        if (e >= 0) atomicAdd(&s_tt.fill[e], 1u);
+        else atomicAdd(&ws.tile_fill[t], 1u);
+      }
+    });
+    if (!direct) {
       __syncthreads();
       for (int e = threadIdx.x; e < kTileTable; e += blockDim.x) {
         const uint32_t t = s_tt.key[e];
@@ -251,68 +334,6 @@ __global__ __launch_bounds__(kBlock) void k_project(KParams p, const gsr_camera 
 #pragma unroll
       for (int q = 0; q < 4; q++)
         if (slot[q] >= 0) rk[q] += s_tt.base[slot[q]];
-    } else {
-      // When the wavefront's records sit close together on the tile grid
-      // (Gaussians stored in spatial order), lanes that share a tile take one
-      // atomic for all of them, ranked by lane within it; otherwise, and for
-      // what a few rounds leave, one atomic per (record, tile).
-      int32_t tmin = vis ? t_first : INT32_MAX, tmax = vis ? t_first : -1;
-  #pragma unroll
-      for (int m = 1; m < 64; m <<= 1) {
-        tmin = min(tmin, __shfl_xor(tmin, m));
-        tmax = max(tmax, __shfl_xor(tmax, m));
-      }
-      const bool gather = tmax - tmin <= 2 * vi.tiles_x + 2;
-      // Group the lanes that share a tile (per rank slot q) with ballots only:
-      // which group no atomic result decides, so the groups are formed first,
-      // each group's lowest lane then takes one atomic for the group, and all
-      // of a lane's atomics are in flight together.  Lanes left after the
-      // rounds, or all lanes when the wavefront is spread out, form groups of
-      // one.
-      int32_t tq[4];
-      bool pending[4];
-      int ldr[4];
-      uint32_t off[4], cnt[4];
-  #pragma unroll
-      for (int q = 0; q < 4; q++) {
-        tq[q] = q < ntiles ? tile_q(q) : -1;
-        pending[q] = tq[q] >= 0;
-        ldr[q] = lane;
-        off[q] = 0u;
-        cnt[q] = 0u;
-      }
-      for (int round = 0; gather && round < 8; round++) {
-        bool any = false;
-  #pragma unroll
-        for (int q = 0; q < 4; q++) {
-          const uint64_t act = __ballot(pending[q]);
-          if (act == 0ull) continue;
-          any = true;
-          const int L = __ffsll((unsigned long long)act) - 1;
-          const int32_t lt = __shfl(tq[q], L);
-          const bool same = pending[q] && tq[q] == lt;
-          const uint64_t m = __ballot(same);
-          if (same) {
-            ldr[q] = L;
-            off[q] = (uint32_t)__popcll(m & below);
-            pending[q] = false;
-          }
-          if (lane == L) cnt[q] = (uint32_t)__popcll(m);
-        }
-        if (!any) break;
-      }
-      uint32_t base[4];
-  #pragma unroll
-      for (int q = 0; q < 4; q++) {
-        if (pending[q]) cnt[q] = 1u;  // a group of one (ldr = lane, off = 0)
-        base[q] = cnt[q] ? atomicAdd(&ws.tile_count[tq[q]], cnt[q]) : 0u;
-      }
-  #pragma unroll
-      for (int q = 0; q < 4; q++) rk[q] = __shfl(base[q], ldr[q]) + off[q];
-      wave_expand(over, [&](int src, uint32_t k, bool live) {
-        const int32_t t = tile_of(src, k + 4u);
-        if (live) atomicAdd(&ws.tile_fill[t], 1u);
-      });
     }
     if (vis) {
       // the record's slot in one 64-byte write: cleared gradient, ranks, rectangle, depth
@@ -332,10 +353,9 @@ __global__ __launch_bounds__(kBlock) void k_project(KParams p, const gsr_camera 
   for (int k = 0; k < 3 * K; k++) sh[k] = p.sh[(int64_t)k * n + i];
   for (uint32_t b = fresh; b; b &= b - 1) {
     const int v = __ffs(b) - 1;
-    const Cam64 &cam = s_cam[v];
     double d[3];
 #pragma unroll
-    for (int a = 0; a < 3; a++) d[a] = g.mu[a] + cam.cc[a];
+    for (int a = 0; a < 3; a++) d[a] = g.mu[a] + s_cc[v][a];
     const double idn = 1.0 / sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
     float Y[K];
     sh_eval<D, float>((float)(d[0] * idn), (float)(d[1] * idn), (float)(d[2] * idn), Y);
@@ -1169,23 +1189,45 @@ __global__ __launch_bounds__(kBlock) void k_project_bwd(KParams p, const gsr_cam
 
 // -------------------------------------------------------------- visibility
 
-__global__ __launch_bounds__(kBlock) void k_visibility(KParams p, const gsr_camera *cams, KOpts o, KWs ws,
-                                                       float bx0, float by0, float bz0, float bx1, float by1,
-                                                       float bz1, uint32_t *bits_out, uint8_t *keep_out,
-                                                       uint8_t *in_block) {
-  __shared__ Cam64 s_cam[GSR_MAX_VIEWS];
-  load_cams(s_cam, cams, ws.views, p.n_views, o);
+// Bound by float64 issue: a pair costs the cull's 40 operations, and the exact
+// projection (200, two divisions, two square roots) only where the cull leaves
+// the decision to it, at the borders of a view.  8 M Gaussians against 32
+// views: 0.93 ms with a division and a square root in the cull, the cameras
+// in LDS and every pair that was not culled projected; 0.40 ms so.
+__global__ __launch_bounds__(kBlock) void k_visibility(KParams p, KOpts o, KWs ws, float bx0, float by0, float bz0,
+                                                       float bx1, float by1, float bz1, uint32_t *bits_out,
+                                                       uint8_t *keep_out, uint8_t *in_block) {
+  const CamPtr cams = cam_ptr(ws);
   const int64_t n = p.n;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const bool keep = p.keep == nullptr || p.keep[i] != 0;
   uint32_t bits = 0;
   if (keep) {
-    GeoF g;
-    load_geo_fwd(p, i, g);
+    double mu[3], ls[3], qq = 0.0;
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+      mu[a] = (double)p.means[a * n + i];
+      ls[a] = (double)p.log_scales[a * n + i];
+    }
+#pragma unroll
+    for (int a = 0; a < 4; a++) qq = __fma_rn((double)p.quats[a * n + i], (double)p.quats[a * n + i], qq);
+    // (a NaN scale never shows the Gaussian, so the bound may leave it out)
+    const double smax = exp(fmax(fmax(ls[0], ls[1]), ls[2]));
+    const bool sane = (ls[0] + ls[1] + ls[2]) * 0.0 == 0.0 && qq > 1.0e-30 && qq < 1.0e30;
+    uint32_t maybe = 0;
     for (int v = 0; v < p.n_views; v++) {
-      Proj P;
-      if (maybe_visible(g, s_cam[v], o) && project_view(g, s_cam[v], o, P)) bits |= 1u << v;
+      const Cull c = cull_view<true>(mu, smax, sane, cams[v], o);
+      bits |= (c == kIn ? 1u : 0u) << v;
+      maybe |= (c == kMaybe ? 1u : 0u) << v;
+    }
+    if (maybe) {
+      GeoF g;
+      load_geo_fwd(p, i, g);
+      for (int v = 0; v < p.n_views; v++) {
+        Proj P;
+        if (((maybe >> v) & 1u) && project_view(g, cams[v], o, P)) bits |= 1u << v;
+      }
     }
   }
   if (bits_out) bits_out[i] = bits;
@@ -1227,15 +1269,13 @@ int launch_fill_f32(float *p, float value, int64_t count, void *stream) {
   return last_err();
 }
 
-int launch_project(const KParams &p, const gsr_camera *cams, const KOpts &o, const KWs &ws, int view_lo,
-                   int view_hi, int or_bits, int table, void *stream) {
+// (the cameras of this step and of launch_visibility's are the set-up kernel's, in the workspace)
+int launch_project(const KParams &p, const gsr_camera *, const KOpts &o, const KWs &ws, int view_lo, int view_hi,
+                   int or_bits, int table, void *stream) {
   const dim3 grid(grid_for(p.n)), block(kBlock);
   hipStream_t s = (hipStream_t)stream;
-#define GSR_PROJECT(D_)                                                                                        \
-  do {                                                                                                        \
-    if (table) hipLaunchKernelGGL((k_project<D_, true>), grid, block, 0, s, p, cams, o, ws, view_lo, view_hi, or_bits); \
-    else hipLaunchKernelGGL((k_project<D_, false>), grid, block, 0, s, p, cams, o, ws, view_lo, view_hi, or_bits);      \
-  } while (0)
+#define GSR_PROJECT(D_) \
+  hipLaunchKernelGGL(k_project<D_>, grid, block, 0, s, p, o, ws, view_lo, view_hi, or_bits, table)
   switch (p.sh_degree) {
     case 0: GSR_PROJECT(0); break;
     case 1: GSR_PROJECT(1); break;
@@ -1300,9 +1340,9 @@ int launch_loss(const KWs &ws, int n_views, float *loss, void *stream) {
   return last_err();
 }
 
-int launch_visibility(const KParams &p, const gsr_camera *cams, const KOpts &o, const KWs &ws, const float *aabb6,
+int launch_visibility(const KParams &p, const gsr_camera *, const KOpts &o, const KWs &ws, const float *aabb6,
                       uint32_t *bits, uint8_t *keep_out, uint8_t *in_block, void *stream) {
-  hipLaunchKernelGGL(k_visibility, dim3(grid_for(p.n)), dim3(kBlock), 0, (hipStream_t)stream, p, cams, o, ws,
+  hipLaunchKernelGGL(k_visibility, dim3(grid_for(p.n)), dim3(kBlock), 0, (hipStream_t)stream, p, o, ws,
                      aabb6[0], aabb6[1], aabb6[2], aabb6[3], aabb6[4], aabb6[5], bits, keep_out, in_block);
   return last_err();
 }
