@@ -95,7 +95,7 @@ void compute_layout(gsr_plan &p) {
   take(L.tile_start, sizeof(uint32_t) * (size_t)(tmax + 1));
   take(L.tile_fill, sizeof(uint32_t) * (size_t)tmax);
   take(L.tile_loss, sizeof(float) * (size_t)tmax);
-  // the schedule order; before the sort, the scan's chunk sums (8 bytes per 4096 tiles)
+  // the schedule order; before it, the sort's list of the longest tiles
   take(L.tile_order, std::max(sizeof(uint32_t) * (size_t)tmax, sizeof(uint64_t) * (size_t)(tmax / 4096 + 2)));
   take(L.keys, sizeof(uint64_t) * (size_t)L.capacity);
   take(L.keys_alt, sizeof(uint64_t) * (size_t)L.capacity);
@@ -249,6 +249,7 @@ KWs ws_view(const gsr_plan &p, void *ws) {
   k.pixels_total = L.pixels_total;
   k.capacity = L.capacity;
   k.history_entries = L.history_entries;
+  k.n_views = p.prob.n_views;
   return k;
 }
 
@@ -761,9 +762,11 @@ gsr_status gsr_query_counts(gsr_plan *plan, const void *ws, gsr_counts *c, void 
   memset(c, 0, sizeof *c);
   for (int v = 0; v < plan->prob.n_views; v++) {
     c->visible[v] = h.visible[v];
-    c->intersections[v] = h.isect[v];
+    // (a view that was not scanned has no later start)
+    const uint64_t a = h.vstart[v], b = h.vstart[v + 1];
+    c->intersections[v] = (int64_t)std::min<uint64_t>(b > a ? b - a : 0, 0xffffffffu);
     c->visible_total += h.visible[v];
-    c->intersections_total += h.isect[v];
+    c->intersections_total += c->intersections[v];
   }
   c->visible_union = h.union_count;
   c->overflow = h.overflow ? 1 : 0;

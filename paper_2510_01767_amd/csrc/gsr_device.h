@@ -392,6 +392,12 @@ __device__ __forceinline__ const float4 *rec_ptr(const KWs &ws, int64_t r) {
   return reinterpret_cast<const float4 *>(ws.records) + r * kRecordFloat4;
 }
 
+// Bin of a list length in the longest-list-first schedule: four lengths a bin,
+// the longest in bin 0.
+__device__ __forceinline__ int order_bin(uint32_t len) {
+  return kOrderBins - 1 - (int)min(len >> 2, (uint32_t)(kOrderBins - 1));
+}
+
 // Global tile id -> view (linear search over at most 32 views).
 __device__ __forceinline__ int view_of_tile(const ViewInfo *views, int n_views, int64_t t) {
   int v = 0;

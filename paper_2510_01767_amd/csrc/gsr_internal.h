@@ -58,13 +58,13 @@ struct WsHeader {
   uint32_t nonfinite;
   uint32_t union_count;   // Gaussians visible in >= 1 view
   uint32_t isect_total;
-  // the per-tile sort's lists, collected per sort call: runs of 2048 keys
+  // the per-tile sort's lists, collected per scan: runs of 2048 keys
   // (tiles of 1025..2048 entries), of 4096 (2049..4096), of 8192 (the runs
   // of longer tiles), and the tiles longer than one run (merged in global
   // memory, taken from the work counter big_next)
   uint32_t run2_count, run_count, run8_count;
   uint32_t big_count, big_next;
-  uint32_t isect[GSR_MAX_VIEWS];
+  uint32_t isect[GSR_MAX_VIEWS];  // plain form: the scanned view's entries
   uint32_t visible[GSR_MAX_VIEWS];
   // longest-list-first schedule of the persistent raster: tiles per length
   // bin (descending) and the bins' fill cursors
@@ -73,9 +73,14 @@ struct WsHeader {
   // persistent raster work counters, one per workgroup class (blockIdx mod
   // 8), each in a 128-byte line of its own
   uint32_t queue[8][32];
-  // per-view loss sums (scaled), added up in view order for the loss
+  // per-view loss sums (scaled), added up in view order for the loss by the
+  // last view's workgroup to finish
+  uint32_t loss_done, pad;
   double view_loss[GSR_MAX_VIEWS];
   Cam64 cams[GSR_MAX_VIEWS];
+  // first list slot of every view (not clamped to the capacity), and the slot
+  // after the last scanned view's
+  uint64_t vstart[GSR_MAX_VIEWS + 1];
 };
 constexpr int kOrderBins = 1024;
 
@@ -127,6 +132,7 @@ struct KWs {
   float *pix_dLdC;
   float *history;
   int64_t vn, tiles_total, pixels_total, capacity, history_entries;
+  int64_t n_views;
 };
 
 // ---------------------------------------------------------------- launchers

@@ -37,13 +37,19 @@ __global__ void k_setup(ViewTable table, KWs ws, int64_t zlo, int64_t zcount, in
     h->nonfinite = 0;
     h->union_count = 0;
     h->isect_total = 0;
+    h->loss_done = 0;
   }
   if (gid < 8) ws.hdr->queue[gid][0] = 0;
   if (gid < GSR_MAX_VIEWS) {
     ws.hdr->isect[gid] = 0;
     ws.hdr->visible[gid] = 0;
+    ws.hdr->vstart[gid] = 0;
   }
-  for (int64_t k = gid; k < kOrderBins; k += stride) ws.hdr->order_bins[k] = 0;
+  if (gid == 0) ws.hdr->vstart[GSR_MAX_VIEWS] = 0;
+  for (int64_t k = gid; k < kOrderBins; k += stride) {
+    ws.hdr->order_bins[k] = 0;
+    ws.hdr->order_cursor[k] = 0;
+  }
   for (int64_t k = gid; k < zcount; k += stride) {
     ws.tile_count[zlo + k] = 0;
     ws.tile_fill[zlo + k] = 0;
@@ -405,11 +411,15 @@ int launch_count_visible(const KWs &ws, int64_t n, int n_views, void *stream) {
 }
 
 // --------------------------------------------------------------------- scan
-// One workgroup of 1024 threads scans tile_count[lo, hi) into tile_start
-// (absolute slots, starting at `base`), writes tile_start[hi], the per-view
-// intersection counts and the overflow flag.
+// Exclusive scan of the tile counts (plus overflow counts) over [lo, hi) into
+// tile_start (absolute slots, starting at `base`), tile_start[hi], the
+// per-view intersection counts and the overflow flag; what the next stages
+// need of the list lengths comes out of the same pass: the sort's lists of
+// long tiles and the histogram of the longest-list-first schedule.
 
 constexpr int kScanThreads = 1024;
+constexpr int kWaveSortMax = 1024;  // 64 lanes x 16 keys: the longest tile one wavefront sorts
+constexpr int kRunLong = 8192;      // the runs of tiles longer than 4096
 
 // Inclusive sum over the 64 lanes of a wavefront (Hillis-Steele with shuffles).
 __device__ __forceinline__ uint64_t wave_incl_scan(uint64_t x) {
@@ -424,118 +434,227 @@ __device__ __forceinline__ uint64_t wave_incl_scan(uint64_t x) {
 
 // Three passes over chunks of kScanChunk consecutive tiles (counts plus
 // overflow counts): the sum of every chunk, then one workgroup scans the chunk
-// sums and finds where each view starts, then every chunk scans itself from
-// its prefix.  The chunk sums live in the tile-order array, which is written
-// only after the sort.  No workgroup waits on another.
+// sums, then every chunk scans itself from its prefix.  No workgroup waits on another.  Up to kScanOne chunks take one
+// workgroup and one launch instead (k_scan_one).
 constexpr int kScanChunk = 4 * kScanThreads;
+constexpr int kScanOne = 3;
 
-__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t x) {
-#pragma unroll
-  for (int m = 1; m < 64; m <<= 1) x += __shfl_xor(x, m);
-  return x;
+// The chunk sums live in the image gradients of the scanned views, which the
+// plain form writes only after them: 12 bytes a pixel and a pixel a tile or
+// more, against 8 bytes per kScanChunk tiles (and the alignment to 8).
+__device__ __forceinline__ uint64_t *chunk_sums(const KWs &ws, int view_lo) {
+  const uintptr_t at = (uintptr_t)(ws.pix_dLdC + 3 * ws.views[view_lo].pix_base);
+  return reinterpret_cast<uint64_t *>((at + 7) & ~(uintptr_t)7);
 }
 
-// Sum over the workgroup (kScanThreads threads); every thread gets it.
-__device__ __forceinline__ uint64_t block_sum_u64(uint64_t x, uint64_t *s_w) {
+// Exclusive prefix of x over the workgroup (kScanThreads threads) and, in
+// `total`, the sum.
+__device__ __forceinline__ uint64_t block_excl_scan(uint64_t x, uint64_t *s_wave, uint64_t &total) {
   constexpr int kWaves = kScanThreads / 64;
-  x = wave_sum_u64(x);
+  const int wave = threadIdx.x >> 6;
+  const uint64_t incl = wave_incl_scan(x);
   __syncthreads();
-  if (lane_id() == 0) s_w[threadIdx.x >> 6] = x;
+  if (lane_id() == 63) s_wave[wave] = incl;
   __syncthreads();
-  uint64_t t = 0;
+  uint64_t before = 0;
+  total = 0;
 #pragma unroll
-  for (int w = 0; w < kWaves; w++) t += s_w[w];
-  return t;
+  for (int w = 0; w < kWaves; w++) {
+    before += w < wave ? s_wave[w] : 0ull;
+    total += s_wave[w];
+  }
+  return before + incl - x;
 }
 
 __device__ __forceinline__ uint32_t tile_total(const KWs &ws, int64_t t, int64_t hi) {
   return t < hi ? ws.tile_count[t] + ws.tile_fill[t] : 0u;
 }
 
-__global__ __launch_bounds__(kScanThreads) void k_scan_sums(KWs ws, int64_t lo, int64_t hi) {
-  __shared__ uint64_t s_w[kScanThreads / 64];
-  const int64_t t0 = lo + (int64_t)blockIdx.x * kScanChunk + 4 * (int64_t)threadIdx.x;
-  uint64_t x = 0;
-#pragma unroll
-  for (int q = 0; q < 4; q++) x += tile_total(ws, t0 + q, hi);
-  const uint64_t sum = block_sum_u64(x, s_w);
-  if (threadIdx.x == 0) reinterpret_cast<uint64_t *>(ws.tile_order)[blockIdx.x] = sum;
+// What every scan leaves besides the tiles' starts: `total` is the slot after
+// the last tile's.  One thread calls it.
+__device__ __forceinline__ void scan_totals(const KWs &ws, int64_t hi, int64_t base, uint64_t total, int view_lo,
+                                            int view_hi) {
+  const uint64_t cap = (uint64_t)ws.capacity;
+  ws.tile_start[hi] = (uint32_t)min(total, cap);
+  if (total > cap) ws.hdr->overflow = 1u;
+  ws.hdr->isect_total = (uint32_t)min(total, (uint64_t)0xffffffffu);
+  ws.hdr->vstart[view_hi] = total;
+  // (the plain form's read-back)
+  if (view_hi == view_lo + 1) ws.hdr->isect[view_lo] = (uint32_t)min(total - (uint64_t)base, (uint64_t)0xffffffffu);
 }
 
-__global__ __launch_bounds__(kScanThreads) void k_scan_chunks(KWs ws, int64_t lo, int64_t hi, int64_t base,
-                                                               int view_lo, int view_hi, int nchunks) {
-  constexpr int kWaves = kScanThreads / 64;
-  __shared__ uint64_t s_wave[kWaves];
-  __shared__ uint64_t s_vstart[GSR_MAX_VIEWS];
-  uint64_t *sums = reinterpret_cast<uint64_t *>(ws.tile_order);
-  const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+// The slot where each view's first tile starts, written by the thread that has
+// that tile among its four from t0 on (starting at `pre`).
+__device__ __forceinline__ void view_starts(const KWs &ws, int64_t t0, const uint32_t x[4], uint64_t pre, int view_lo,
+                                            int view_hi) {
+  for (int v = view_lo; v < view_hi; v++) {
+    const int64_t d = ws.views[v].tile_base - t0;
+    if (d >= 0 && d < 4) ws.hdr->vstart[v] = pre + (d > 0 ? x[0] : 0u) + (d > 1 ? x[1] : 0u) + (d > 2 ? x[2] : 0u);
+  }
+}
+
+// Runs of the tiles longer than one wavefront's register sort, listed by the
+// scan in keys_alt (tile ids of the 2048-key runs from word 0, of the
+// 4096-key runs from word capacity / 2, (tile, run index) pairs of the
+// 8192-key runs from word `capacity`), which the merge passes use only after
+// the runs are sorted; the tiles longer than one run in tile_order (free
+// between the projection and the schedule).
+__device__ __forceinline__ uint32_t *run_list(const KWs &ws, int run) {
+  return reinterpret_cast<uint32_t *>(ws.keys_alt) + (run == 2048 ? 0 : run == 4096 ? ws.capacity / 2 : ws.capacity);
+}
+
+// One atomic per wavefront and list, the lanes' places following from a
+// prefix sum over the wavefront: a single counter hit by every long tile of
+// a 2160p view would serialise on its address.
+__device__ __forceinline__ uint32_t wave_append(uint32_t *counter, uint32_t count) {
+  if (__ballot(count != 0u) == 0ull) return 0u;
+  const int lane = lane_id();
+  uint32_t incl = count;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t y = __shfl_up(incl, (unsigned)off);
+    if (lane >= off) incl += y;
+  }
+  uint32_t base = 0u;
+  if (lane == 63) base = atomicAdd(counter, incl);
+  return (uint32_t)__builtin_amdgcn_readlane((int)base, 63) + incl - count;
+}
+
+__device__ __forceinline__ void reset_run_lists(const KWs &ws) {
+  ws.hdr->big_count = 0u;
+  ws.hdr->big_next = 0u;
+  ws.hdr->run2_count = 0u;
+  ws.hdr->run_count = 0u;
+  ws.hdr->run8_count = 0u;
+}
+
+// One chunk of the scan: this thread's four tiles from t0 on, their first slot
+// `pre`.  Every thread of the workgroup calls it.  s_hist (kOrderBins words,
+// or null where no schedule follows) receives the list lengths.
+__device__ __forceinline__ void scan_chunk(const KWs &ws, int64_t t0, int64_t hi, const uint32_t x[4], uint64_t pre,
+                                           uint32_t *s_hist) {
+  const uint64_t cap = (uint64_t)ws.capacity;
+  uint32_t len[4], n2 = 0u, n4 = 0u, n8 = 0u, nb = 0u;
+#pragma unroll
+  for (int q = 0; q < 4; q++) {
+    const uint64_t start = min(pre, cap), end = min(pre + x[q], cap);
+    pre += x[q];
+    len[q] = t0 + q < hi ? (uint32_t)(end - start) : 0u;
+    if (t0 + q < hi) {
+      ws.tile_start[t0 + q] = (uint32_t)start;
+      if (s_hist) atomicAdd(&s_hist[order_bin(len[q])], 1u);
+    }
+    n2 += len[q] > kWaveSortMax && len[q] <= 2048u;
+    n4 += len[q] > 2048u && len[q] <= 4096u;
+    n8 += len[q] > 4096u ? (len[q] + kRunLong - 1) / kRunLong : 0u;
+    nb += len[q] > kRunLong;
+  }
+  uint32_t a2 = wave_append(&ws.hdr->run2_count, n2), a4 = wave_append(&ws.hdr->run_count, n4);
+  uint32_t a8 = wave_append(&ws.hdr->run8_count, n8), ab = wave_append(&ws.hdr->big_count, nb);
+  if (n2 + n4 + n8 == 0u) return;
+#pragma unroll
+  for (int q = 0; q < 4; q++) {
+    const uint32_t t = (uint32_t)(t0 + q);
+    if (len[q] > 4096u) {
+      uint32_t *list = run_list(ws, kRunLong);
+      for (uint32_t c = 0; c * kRunLong < len[q]; c++, a8++) {
+        list[2 * a8] = t;
+        list[2 * a8 + 1] = c;
+      }
+      if (len[q] > kRunLong) ws.tile_order[ab++] = t;
+    } else if (len[q] > 2048u) {
+      run_list(ws, 4096)[a4++] = t;
+    } else if (len[q] > kWaveSortMax) {
+      run_list(ws, 2048)[a2++] = t;
+    }
+  }
+}
+
+__device__ __forceinline__ void hist_clear(uint32_t *s_hist) {
+  for (int k = threadIdx.x; k < kOrderBins; k += blockDim.x) s_hist[k] = 0u;
+}
+
+__device__ __forceinline__ void hist_add(const KWs &ws, const uint32_t *s_hist) {
+  for (int k = threadIdx.x; k < kOrderBins; k += blockDim.x)
+    if (s_hist[k]) atomicAdd(&ws.hdr->order_bins[k], s_hist[k]);
+}
+
+__global__ __launch_bounds__(kScanThreads) void k_scan_sums(KWs ws, int64_t lo, int64_t hi, int view_lo) {
+  __shared__ uint64_t s_wave[kScanThreads / 64];
+  const int64_t t0 = lo + (int64_t)blockIdx.x * kScanChunk + 4 * (int64_t)threadIdx.x;
+  uint64_t x = 0, sum;
+#pragma unroll
+  for (int q = 0; q < 4; q++) x += tile_total(ws, t0 + q, hi);
+  block_excl_scan(x, s_wave, sum);
+  if (threadIdx.x == 0) {
+    chunk_sums(ws, view_lo)[blockIdx.x] = sum;
+    if (blockIdx.x == 0) reset_run_lists(ws);
+  }
+}
+
+__global__ __launch_bounds__(kScanThreads) void k_scan_chunks(KWs ws, int64_t hi, int64_t base, int view_lo,
+                                                               int view_hi, int nchunks) {
+  __shared__ uint64_t s_wave[kScanThreads / 64];
+  uint64_t *sums = chunk_sums(ws, view_lo);
+  const int tid = threadIdx.x;
   // exclusive scan of the chunk sums (at most kScanChunk chunks), plus base
-  uint64_t x[4];
+  uint64_t x[4], total;
 #pragma unroll
   for (int q = 0; q < 4; q++) x[q] = 4 * tid + q < nchunks ? sums[4 * tid + q] : 0ull;
-  const uint64_t s = x[0] + x[1] + x[2] + x[3];
-  const uint64_t incl = wave_incl_scan(s);
-  if (lane == 63) s_wave[wave] = incl;
-  __syncthreads();
-  uint64_t before = 0;
-  for (int w = 0; w < wave; w++) before += s_wave[w];
-  uint64_t pre = (uint64_t)base + before + (incl - s);
-  uint64_t total = (uint64_t)base;
-  for (int w = 0; w < kWaves; w++) total += s_wave[w];
-  __syncthreads();
+  uint64_t pre = (uint64_t)base + block_excl_scan(x[0] + x[1] + x[2] + x[3], s_wave, total);
 #pragma unroll
   for (int q = 0; q < 4; q++) {
     if (4 * tid + q < nchunks) sums[4 * tid + q] = pre;
     pre += x[q];
   }
-  __syncthreads();
-  // where each view's first tile starts: its chunk's prefix plus the counts
-  // in front of it within the chunk (one wavefront per view, all at once)
-  const int nv = view_hi - view_lo;
-  for (int v = wave; v < nv; v += kWaves) {
-    const int64_t tb = ws.views[view_lo + v].tile_base;
-    const int64_t c = (tb - lo) / kScanChunk;
-    const int64_t c0 = lo + c * kScanChunk;
-    uint64_t part = 0;
-    for (int64_t t = c0 + lane; t < tb; t += 64) part += tile_total(ws, t, hi);
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) part += __shfl_xor(part, m);
-    if (lane == 0) s_vstart[v] = sums[c] + part;
-  }
-  __syncthreads();
-  const uint64_t cap = (uint64_t)ws.capacity;
-  if (tid == 0) {
-    ws.tile_start[hi] = (uint32_t)min(total, cap);
-    if (total > cap) ws.hdr->overflow = 1u;
-    ws.hdr->isect_total = (uint32_t)min(total, (uint64_t)0xffffffffu);
-  }
-  if (tid < nv) {
-    const uint64_t a = s_vstart[tid], b = tid + 1 < nv ? s_vstart[tid + 1] : total;
-    ws.hdr->isect[view_lo + tid] = (uint32_t)min(b - a, (uint64_t)0xffffffffu);
-  }
+  if (tid == 0) scan_totals(ws, hi, base, (uint64_t)base + total, view_lo, view_hi);
 }
 
-__global__ __launch_bounds__(kScanThreads) void k_scan_apply(KWs ws, int64_t lo, int64_t hi) {
-  constexpr int kWaves = kScanThreads / 64;
-  __shared__ uint64_t s_wave[kWaves];
-  const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
-  const int64_t t0 = lo + (int64_t)blockIdx.x * kScanChunk + 4 * (int64_t)tid;
+__global__ __launch_bounds__(kScanThreads) void k_scan_apply(KWs ws, int64_t lo, int64_t hi, int view_lo,
+                                                              int view_hi, int schedule) {
+  __shared__ uint64_t s_wave[kScanThreads / 64];
+  __shared__ uint32_t s_hist[kOrderBins];
+  const int64_t t0 = lo + (int64_t)blockIdx.x * kScanChunk + 4 * (int64_t)threadIdx.x;
+  hist_clear(s_hist);
   uint32_t x[4];
 #pragma unroll
   for (int q = 0; q < 4; q++) x[q] = tile_total(ws, t0 + q, hi);
-  const uint64_t s = (uint64_t)x[0] + x[1] + x[2] + x[3];
-  const uint64_t incl = wave_incl_scan(s);
-  if (lane == 63) s_wave[wave] = incl;
+  uint64_t total;
+  const uint64_t pre =
+      chunk_sums(ws, view_lo)[blockIdx.x] + block_excl_scan((uint64_t)x[0] + x[1] + x[2] + x[3], s_wave, total);
+  view_starts(ws, t0, x, pre, view_lo, view_hi);
+  scan_chunk(ws, t0, hi, x, pre, schedule ? s_hist : nullptr);
   __syncthreads();
-  uint64_t before = 0;
-  for (int w = 0; w < wave; w++) before += s_wave[w];
-  uint64_t pre = reinterpret_cast<const uint64_t *>(ws.tile_order)[blockIdx.x] + before + (incl - s);
-  const uint64_t cap = (uint64_t)ws.capacity;
-#pragma unroll
-  for (int q = 0; q < 4; q++) {
-    if (t0 + q < hi) ws.tile_start[t0 + q] = (uint32_t)min(pre, cap);
-    pre += x[q];
+  if (schedule) hist_add(ws, s_hist);
+}
+
+// The whole scan by one workgroup, chunk after chunk: the launches of the
+// three-pass form cost more than the chunks (14 us for one chunk of three
+// launches, 7 us so).
+__global__ __launch_bounds__(kScanThreads) void k_scan_one(KWs ws, int64_t lo, int64_t hi, int64_t base, int view_lo,
+                                                            int view_hi, int schedule) {
+  __shared__ uint64_t s_wave[kScanThreads / 64];
+  __shared__ uint32_t s_hist[kOrderBins];
+  hist_clear(s_hist);
+  if (threadIdx.x == 0) {
+    reset_run_lists(ws);
+    __threadfence();  // before the other wavefronts' appends, past the barriers of the first chunk
   }
+  uint64_t carry = (uint64_t)base;
+  for (int64_t c0 = lo; c0 < hi; c0 += kScanChunk) {
+    const int64_t t0 = c0 + 4 * (int64_t)threadIdx.x;
+    uint32_t x[4];
+#pragma unroll
+    for (int q = 0; q < 4; q++) x[q] = tile_total(ws, t0 + q, hi);
+    uint64_t total;
+    const uint64_t pre = carry + block_excl_scan((uint64_t)x[0] + x[1] + x[2] + x[3], s_wave, total);
+    view_starts(ws, t0, x, pre, view_lo, view_hi);
+    scan_chunk(ws, t0, hi, x, pre, schedule ? s_hist : nullptr);
+    carry += total;
+  }
+  if (threadIdx.x == 0) scan_totals(ws, hi, base, carry, view_lo, view_hi);
+  __syncthreads();
+  if (schedule) hist_add(ws, s_hist);
 }
 
 // --------------------------------------------------------------------- emit
@@ -608,9 +727,7 @@ __global__ __launch_bounds__(kBlock) void k_emit(KWs ws, int64_t n, int n_views,
 // in registers as above) and one to three merge levels in LDS.  Tiles
 // longer than one run are then merged run by run in global memory.
 
-constexpr int kWaveSortMax = 1024;  // 64 lanes x 16 keys
 constexpr int kSortBigThreads = 1024;
-constexpr int kRunLong = 8192;      // the runs of tiles longer than 4096
 
 template <int CTRL>
 __device__ __forceinline__ uint64_t dpp_u64(uint64_t x) {
@@ -766,71 +883,6 @@ __device__ void merge_tile_block(const KWs &ws, int64_t t) {
   __syncthreads();
 }
 
-// Runs of the tiles longer than one wavefront's register sort, listed per
-// sort call in keys_alt (tile ids of the 2048-key runs from word 0, of the
-// 4096-key runs from word capacity / 2, (tile, run index) pairs of the
-// 8192-key runs from word `capacity`), which the merge passes use only after
-// the runs are sorted; the tiles longer than one run in tile_order (free
-// between the scan and the schedule).  Workgroups take the runs in a fixed
-// stride (runs of one size cost alike), then the long tiles from a counter,
-// so long tiles spread over the whole chip.
-__global__ void k_big_reset(KWs ws) {
-  ws.hdr->big_count = 0u;
-  ws.hdr->big_next = 0u;
-  ws.hdr->run2_count = 0u;
-  ws.hdr->run_count = 0u;
-  ws.hdr->run8_count = 0u;
-}
-
-__device__ __forceinline__ uint32_t *run_list(const KWs &ws, int run) {
-  return reinterpret_cast<uint32_t *>(ws.keys_alt) + (run == 2048 ? 0 : run == 4096 ? ws.capacity / 2 : ws.capacity);
-}
-
-// One atomic per wavefront and list, the lanes' places following from a
-// prefix sum over the wavefront: a single counter hit by every long tile of
-// a 2160p view would serialise on its address.
-__device__ __forceinline__ uint32_t wave_append(uint32_t *counter, bool take, uint32_t count) {
-  const int lane = lane_id();
-  uint32_t before = 0u, total = 0u;
-  // lanes append `count` entries each; the prefix over lower lanes by shuffles
-  uint32_t c = take ? count : 0u, incl = c;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t y = __shfl_up(incl, (unsigned)off);
-    if (lane >= off) incl += y;
-  }
-  total = __shfl(incl, 63);
-  before = incl - c;
-  uint32_t base = 0u;
-  if (total != 0u && lane == 0) base = atomicAdd(counter, total);
-  return __shfl(base, 0) + before;
-}
-
-__global__ __launch_bounds__(kBlock) void k_big_collect(KWs ws, int64_t tile_lo, int64_t tile_count) {
-  // (every lane of a wavefront goes through the same iterations: the appends are wavefront-wide)
-  for (int64_t b0 = (int64_t)blockIdx.x * blockDim.x; b0 < tile_count; b0 += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t b = b0 + threadIdx.x;
-    const int64_t t = tile_lo + b;
-    const int64_t n = b < tile_count ? (int64_t)ws.tile_start[t + 1] - ws.tile_start[t] : 0;
-    const bool r2 = n > kWaveSortMax && n <= 2048, r4 = n > 2048 && n <= 4096, r8 = n > 4096;
-    const uint32_t runs = r8 ? (uint32_t)((n + kRunLong - 1) / kRunLong) : 0u;
-    const uint32_t a2 = wave_append(&ws.hdr->run2_count, r2, 1u);
-    const uint32_t a4 = wave_append(&ws.hdr->run_count, r4, 1u);
-    const uint32_t a8 = wave_append(&ws.hdr->run8_count, r8, runs);
-    const uint32_t ab = wave_append(&ws.hdr->big_count, n > kRunLong, 1u);
-    if (r2) run_list(ws, 2048)[a2] = (uint32_t)t;
-    if (r4) run_list(ws, 4096)[a4] = (uint32_t)t;
-    if (r8) {
-      uint32_t *list = run_list(ws, kRunLong);
-      for (uint32_t c = 0; c < runs; c++) {
-        list[2 * (a8 + c)] = (uint32_t)t;
-        list[2 * (a8 + c) + 1] = c;
-      }
-    }
-    if (n > kRunLong) ws.tile_order[ab] = (uint32_t)t;
-  }
-}
-
 // One level of merges inside a run of RUN keys in LDS: the sorted blocks of
 // w keys are merged in pairs into blocks of 2w.  Each of the THREADS threads
 // produces RUN / THREADS consecutive outputs after one co-rank search (keys
@@ -864,7 +916,7 @@ __device__ __forceinline__ void merge_level_lds(uint64_t *s, int w) {
   __syncthreads();
 }
 
-// Sorts the listed runs of RUN keys: each wavefront sorts its 1024 keys of
+// Sorts the runs of RUN keys that the scan listed: each wavefront sorts its 1024 keys of
 // the run in registers, then merge levels in LDS give the sorted run.
 // Missing keys of a short run are padded with distinct values above every
 // key, ascending with the position (depth bits of a finite float stay below
@@ -877,7 +929,8 @@ __global__ __launch_bounds__(RUN / 16) void k_sort_runs(KWs ws) {
   const uint32_t count = RUN == 2048 ? ws.hdr->run2_count : RUN == 4096 ? ws.hdr->run_count : ws.hdr->run8_count;
   const uint32_t *list = run_list(ws, RUN);
   const int wave = threadIdx.x >> 6, lane = lane_id();
-  // runs of one size cost alike: workgroups take them in a fixed stride
+  // runs of one size cost alike: workgroups take them in a fixed stride, then
+  // the tiles longer than a run from a counter, so they spread over the chip
   for (uint32_t k = blockIdx.x; k < count; k += gridDim.x) {
     const int64_t t = RUN <= 4096 ? list[k] : list[2 * k];
     const int64_t c0 = RUN <= 4096 ? 0 : (int64_t)list[2 * k + 1] * RUN;
@@ -906,6 +959,7 @@ __global__ __launch_bounds__(RUN / 16) void k_sort_runs(KWs ws) {
 __global__ __launch_bounds__(kSortBigThreads) void k_sort_big(KWs ws) {
   __shared__ uint32_t s_k;
   const uint32_t count = ws.hdr->big_count;
+  if (blockIdx.x >= count) return;  // (no more workgroups than tiles are needed)
   for (;;) {
     if (threadIdx.x == 0) s_k = atomicAdd(&ws.hdr->big_next, 1u);
     __syncthreads();
@@ -918,9 +972,9 @@ __global__ __launch_bounds__(kSortBigThreads) void k_sort_big(KWs ws) {
 // --------------------------------------------------------------- loss total
 
 // Deterministic: fixed thread mapping and reduction tree, double
-// accumulation.  One workgroup per view sums its tiles' losses; one thread
-// then adds the views in order.
-__global__ __launch_bounds__(kScanThreads) void k_loss_views(KWs ws) {
+// accumulation.  One workgroup per view sums its tiles' losses; the last of
+// them to finish adds the views in order.
+__global__ __launch_bounds__(kScanThreads) void k_loss(KWs ws, int n_views, float *loss) {
   constexpr int kWaves = kScanThreads / 64;
   __shared__ double s_w[kWaves];
   const int v = blockIdx.x;
@@ -936,15 +990,15 @@ __global__ __launch_bounds__(kScanThreads) void k_loss_views(KWs ws) {
     double t = 0.0;
 #pragma unroll
     for (int w = 0; w < kWaves; w++) t += s_w[w];
-    ws.hdr->view_loss[v] = t * (double)vi.loss_scale;
-  }
-}
-
-__global__ void k_loss_total(KWs ws, int n_views, float *loss) {
-  if (threadIdx.x == 0) {
-    double total = 0.0;
-    for (int v = 0; v < n_views; v++) total += ws.hdr->view_loss[v];
-    *loss = (float)total;
+    __hip_atomic_store(&ws.hdr->view_loss[v], t * (double)vi.loss_scale, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // (released by this workgroup's count, acquired by the last one's)
+    const uint32_t done = __hip_atomic_fetch_add(&ws.hdr->loss_done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    if (done + 1 == (uint32_t)n_views) {
+      double total = 0.0;
+      for (int u = 0; u < n_views; u++)
+        total += __hip_atomic_load(&ws.hdr->view_loss[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      *loss = (float)total;
+    }
   }
 }
 
@@ -1289,14 +1343,20 @@ int launch_project(const KParams &p, const gsr_camera *, const KOpts &o, const K
 int launch_scan(const KWs &ws, int64_t lo, int64_t hi, int64_t base, int view_lo, int view_hi, void *stream) {
   if (hi <= lo) return (int)hipErrorInvalidValue;
   const int64_t nchunks = (hi - lo + kScanChunk - 1) / kScanChunk;
-  // chunk sums in the tile-order array (sized for 8 bytes per chunk of the
-  // largest tile grid); one workgroup scans at most kScanChunk of them
+  // the one workgroup of the second pass scans at most kScanChunk chunk sums
   if (nchunks > kScanChunk) return (int)hipErrorInvalidValue;
   hipStream_t s = (hipStream_t)stream;
-  hipLaunchKernelGGL(k_scan_sums, dim3((unsigned)nchunks), dim3(kScanThreads), 0, s, ws, lo, hi);
-  hipLaunchKernelGGL(k_scan_chunks, dim3(1), dim3(kScanThreads), 0, s, ws, lo, hi, base, view_lo, view_hi,
+  // the schedule of the persistent raster covers all views at once
+  const int schedule = lo == 0 && hi == ws.tiles_total ? 1 : 0;
+  if (nchunks <= kScanOne) {
+    hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(kScanThreads), 0, s, ws, lo, hi, base, view_lo, view_hi, schedule);
+    return last_err();
+  }
+  hipLaunchKernelGGL(k_scan_sums, dim3((unsigned)nchunks), dim3(kScanThreads), 0, s, ws, lo, hi, view_lo);
+  hipLaunchKernelGGL(k_scan_chunks, dim3(1), dim3(kScanThreads), 0, s, ws, hi, base, view_lo, view_hi,
                      (int)nchunks);
-  hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nchunks), dim3(kScanThreads), 0, s, ws, lo, hi);
+  hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nchunks), dim3(kScanThreads), 0, s, ws, lo, hi, view_lo, view_hi,
+                     schedule);
   return last_err();
 }
 
@@ -1311,13 +1371,13 @@ int launch_sort(const KWs &ws, int64_t tile_lo, int64_t tile_count, void *stream
   hipStream_t s = (hipStream_t)stream;
   const dim3 wgrid((unsigned)xcd_grid((tile_count + 3) / 4));
   hipLaunchKernelGGL(k_sort_wave, wgrid, dim3(kBlock), 0, s, ws, tile_lo, tile_count);
-  hipLaunchKernelGGL(k_big_reset, dim3(1), dim3(1), 0, s, ws);
-  hipLaunchKernelGGL(k_big_collect, dim3((unsigned)min((tile_count + kBlock - 1) / kBlock, (int64_t)4096)),
-                     dim3(kBlock), 0, s, ws, tile_lo, tile_count);
-  hipLaunchKernelGGL(k_sort_runs<2048>, dim3(4096), dim3(128), 0, s, ws);
-  hipLaunchKernelGGL(k_sort_runs<4096>, dim3(2048), dim3(256), 0, s, ws);
-  hipLaunchKernelGGL(k_sort_runs<kRunLong>, dim3(1024), dim3(kRunLong / 16), 0, s, ws);
-  hipLaunchKernelGGL(k_sort_big, dim3(512), dim3(kSortBigThreads), 0, s, ws);
+  // A tile lists each Gaussian of its view at most once: sorts of longer runs
+  // than there are Gaussians are not launched.
+  const int64_t longest = ws.vn / ws.n_views;
+  if (longest > kWaveSortMax) hipLaunchKernelGGL(k_sort_runs<2048>, dim3(4096), dim3(128), 0, s, ws);
+  if (longest > 2048) hipLaunchKernelGGL(k_sort_runs<4096>, dim3(2048), dim3(256), 0, s, ws);
+  if (longest > 4096) hipLaunchKernelGGL(k_sort_runs<kRunLong>, dim3(1024), dim3(kRunLong / 16), 0, s, ws);
+  if (longest > kRunLong) hipLaunchKernelGGL(k_sort_big, dim3(512), dim3(kSortBigThreads), 0, s, ws);
   return last_err();
 }
 
@@ -1335,8 +1395,7 @@ int launch_project_bwd(const KParams &p, const gsr_camera *cams, const KOpts &o,
 }
 
 int launch_loss(const KWs &ws, int n_views, float *loss, void *stream) {
-  hipLaunchKernelGGL(k_loss_views, dim3((unsigned)n_views), dim3(kScanThreads), 0, (hipStream_t)stream, ws);
-  hipLaunchKernelGGL(k_loss_total, dim3(1), dim3(64), 0, (hipStream_t)stream, ws, n_views, loss);
+  hipLaunchKernelGGL(k_loss, dim3((unsigned)n_views), dim3(kScanThreads), 0, (hipStream_t)stream, ws, n_views, loss);
   return last_err();
 }
 

@@ -588,44 +588,36 @@ __global__ __launch_bounds__(kBlock, RED == 0 && !HIST ? 8 : 1) void k_fused(KWs
 // made of short ones.  The order only schedules work: every tile's result is
 // the same whichever workgroup computes it, whenever.
 
-__device__ __forceinline__ int order_bin(const KWs &ws, int64_t t) {
-  const uint32_t n = ws.tile_start[t + 1] - ws.tile_start[t];
-  return kOrderBins - 1 - (int)min(n >> 2, (uint32_t)(kOrderBins - 1));
-}
-
-__global__ __launch_bounds__(kBlock) void k_order_hist(KWs ws) {
-  __shared__ uint32_t s_h[kOrderBins];
-  for (int k = threadIdx.x; k < kOrderBins; k += blockDim.x) s_h[k] = 0;
-  __syncthreads();
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < ws.tiles_total;
-       t += (int64_t)gridDim.x * blockDim.x)
-    atomicAdd(&s_h[order_bin(ws, t)], 1u);
-  __syncthreads();
-  for (int k = threadIdx.x; k < kOrderBins; k += blockDim.x)
-    if (s_h[k]) atomicAdd(&ws.hdr->order_bins[k], s_h[k]);
-}
-
-__global__ __launch_bounds__(kOrderBins) void k_order_scan(KWs ws) {
-  __shared__ uint32_t s[kOrderBins];
-  const int k = threadIdx.x;
-  const uint32_t x = ws.hdr->order_bins[k];
-  s[k] = x;
-  __syncthreads();
-  for (int off = 1; off < kOrderBins; off <<= 1) {
-    const uint32_t y = k >= off ? s[k - off] : 0u;
-    __syncthreads();
-    s[k] += y;
-    __syncthreads();
-  }
-  ws.hdr->order_cursor[k] = s[k] - x;
-}
-
-// Each workgroup places its tiles with one device atomic per bin it holds
-// (the ranks inside the workgroup from LDS atomics): the bins of the many
-// short or empty tiles would otherwise take one atomic per tile on a single
-// address.
+// (the histogram of the list lengths comes out of the scan)
+//
+// Every workgroup scans the 1024 bins for itself, then places its tiles with
+// one device atomic per bin it holds (the ranks inside the workgroup from LDS
+// atomics): the bins of the many short or empty tiles would otherwise take
+// one atomic per tile on a single address.
 __global__ __launch_bounds__(kBlock) void k_order_scatter(KWs ws) {
-  __shared__ uint32_t s_cnt[kOrderBins], s_base[kOrderBins];
+  constexpr int kPer = kOrderBins / kBlock;
+  __shared__ uint32_t s_cnt[kOrderBins], s_base[kOrderBins], s_first[kOrderBins], s_wave[kBlock / 64];
+  uint32_t x[kPer], sum = 0u;
+#pragma unroll
+  for (int k = 0; k < kPer; k++) {
+    x[k] = ws.hdr->order_bins[kPer * threadIdx.x + k];
+    sum += x[k];
+  }
+  uint32_t incl = sum;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t y = __shfl_up(incl, (unsigned)off);
+    if (lane_id() >= off) incl += y;
+  }
+  if (lane_id() == 63) s_wave[threadIdx.x >> 6] = incl;
+  __syncthreads();
+  uint32_t first = incl - sum;
+  for (int w = 0; w < (int)(threadIdx.x >> 6); w++) first += s_wave[w];
+#pragma unroll
+  for (int k = 0; k < kPer; k++) {
+    s_first[kPer * threadIdx.x + k] = first;
+    first += x[k];
+  }
   for (int64_t t0 = (int64_t)blockIdx.x * blockDim.x; t0 < ws.tiles_total; t0 += (int64_t)gridDim.x * blockDim.x) {
     for (int k = threadIdx.x; k < kOrderBins; k += blockDim.x) s_cnt[k] = 0u;
     __syncthreads();
@@ -633,12 +625,12 @@ __global__ __launch_bounds__(kBlock) void k_order_scatter(KWs ws) {
     int bin = -1;
     uint32_t off = 0u;
     if (t < ws.tiles_total) {
-      bin = order_bin(ws, t);
+      bin = order_bin(ws.tile_start[t + 1] - ws.tile_start[t]);
       off = atomicAdd(&s_cnt[bin], 1u);
     }
     __syncthreads();
     for (int k = threadIdx.x; k < kOrderBins; k += blockDim.x)
-      if (s_cnt[k]) s_base[k] = atomicAdd(&ws.hdr->order_cursor[k], s_cnt[k]);
+      if (s_cnt[k]) s_base[k] = s_first[k] + atomicAdd(&ws.hdr->order_cursor[k], s_cnt[k]);
     __syncthreads();
     if (bin >= 0) ws.tile_order[s_base[bin] + off] = (uint32_t)t;
     __syncthreads();
@@ -646,11 +638,8 @@ __global__ __launch_bounds__(kBlock) void k_order_scatter(KWs ws) {
 }
 
 int launch_tile_order(const KWs &ws, void *stream) {
-  hipStream_t s = (hipStream_t)stream;
-  const int g = (int)min((int64_t)256, (ws.tiles_total + kBlock - 1) / kBlock);
-  hipLaunchKernelGGL(k_order_hist, dim3(g), dim3(kBlock), 0, s, ws);
-  hipLaunchKernelGGL(k_order_scan, dim3(1), dim3(kOrderBins), 0, s, ws);
-  hipLaunchKernelGGL(k_order_scatter, dim3(grid_for(ws.tiles_total)), dim3(kBlock), 0, s, ws);
+  const int g = (int)min((int64_t)512, (ws.tiles_total + kBlock - 1) / kBlock);
+  hipLaunchKernelGGL(k_order_scatter, dim3(g), dim3(kBlock), 0, (hipStream_t)stream, ws);
   return last_err();
 }
 
