@@ -321,17 +321,6 @@ ViewTable step_table(const gsr_plan &p, const gsr_camera *cams) {
   return t;
 }
 
-gsr_status zero_grads(gsr_plan *plan, const gsr_grads *g, void *stream) {
-  const int64_t n = plan->prob.n;
-  const int K = (plan->prob.sh_degree + 1) * (plan->prob.sh_degree + 1);
-  STAGE(launch_fill_f32(g->means, 0.f, 3 * n, stream), "fill");
-  STAGE(launch_fill_f32(g->log_scales, 0.f, 3 * n, stream), "fill");
-  STAGE(launch_fill_f32(g->quats, 0.f, 4 * n, stream), "fill");
-  STAGE(launch_fill_f32(g->opacity_logits, 0.f, n, stream), "fill");
-  STAGE(launch_fill_f32(g->sh, 0.f, (int64_t)3 * K * n, stream), "fill");
-  return GSR_OK;
-}
-
 // Project, bin and order every view.  Plain: one chain per view with a
 // read-back of each view's intersection count (the plain form's only sync).
 // Batched: one chain for all views, no host synchronisation.
@@ -400,10 +389,6 @@ gsr_status enqueue_plain_l1(gsr_plan *plan, const gsr_gaussians *g, const gsr_ca
   const KOpts ko = kopts(*plan);
   const int V = plan->prob.n_views;
   const int hist = use_history(*plan) ? 1 : 0;
-  if (!plan->opt.accumulate_grads) {
-    gsr_status s = zero_grads(plan, grads, stream);
-    if (s != GSR_OK) return s;
-  }
   STAGE(launch_setup(tbl, ws, 0, ws.tiles_total, 1, plan->prob.n, stream), "setup");
   int64_t base = 0;
   for (int v = 0; v < V; v++) {
@@ -424,11 +409,15 @@ gsr_status enqueue_plain_l1(gsr_plan *plan, const gsr_gaussians *g, const gsr_ca
     STAGE(launch_l1(ws, ko, vi.tile_base, nt, images, targets, V, stream), "l1");
     STAGE(launch_raster_bwd(ws, ko, vi.tile_base, nt, ws.pix_dLdC, V, hist, plan->opt.lds_batch,
                             plan->opt.bwd_reduce, stream), "raster_bwd");
-    STAGE(launch_project_bwd(kp, cams, ko, ws, kgrads(grads), stats ? stats->grad2d_norm_sum : nullptr,
-                              stats ? stats->visible_count : nullptr, v, stream),
-           "project_bwd");
     base += iv;
   }
+  // The records' gradients of every view are in their slots: one pass takes
+  // them to the parameters, instead of one per view that reads and adds to
+  // every plane (four 1600 x 900 views of 1.5 M Gaussians: 0.44 ms and the
+  // planes' clearing 0.06 -> 0.12 ms).
+  STAGE(launch_project_bwd(kp, cams, ko, ws, kgrads(grads), stats ? stats->grad2d_norm_sum : nullptr,
+                           stats ? stats->visible_count : nullptr, -1, stream),
+        "project_bwd");
   STAGE(launch_loss(ws, V, loss, stream), "loss");
   return GSR_OK;
 }
@@ -640,23 +629,10 @@ gsr_status gsr_backward(gsr_plan *plan, const gsr_gaussians *g, const gsr_camera
   const int V = plan->prob.n_views;
   float *sS = stats ? stats->grad2d_norm_sum : nullptr;
   uint32_t *sN = stats ? stats->visible_count : nullptr;
-  if (plan->opt.mode == GSR_MODE_PLAIN) {
-    if (!plan->opt.accumulate_grads) {
-      s = zero_grads(plan, grads, stream);
-      if (s != GSR_OK) return s;
-    }
-    const ViewTable tbl = view_table(*plan);
-    for (int v = 0; v < V; v++) {
-      const int64_t nt = (int64_t)tbl.v[v].tiles_x * tbl.v[v].tiles_y;
-      STAGE(launch_raster_bwd(k, ko, tbl.v[v].tile_base, nt, dL_dimages, V, hist, plan->opt.lds_batch,
-                              plan->opt.bwd_reduce, stream), "raster_bwd");
-      STAGE(launch_project_bwd(kp, cams, ko, k, kgrads(grads), sS, sN, v, stream), "project_bwd");
-    }
-  } else {
-    STAGE(launch_raster_bwd(k, ko, 0, k.tiles_total, dL_dimages, V, hist, plan->opt.lds_batch,
-                            plan->opt.bwd_reduce, stream), "raster_bwd");
-    STAGE(launch_project_bwd(kp, cams, ko, k, kgrads(grads), sS, sN, -1, stream), "project_bwd");
-  }
+  STAGE(launch_raster_bwd(k, ko, 0, k.tiles_total, dL_dimages, V, hist, plan->opt.lds_batch, plan->opt.bwd_reduce,
+                          stream),
+        "raster_bwd");
+  STAGE(launch_project_bwd(kp, cams, ko, k, kgrads(grads), sS, sN, -1, stream), "project_bwd");
   plan->forward_ready = false;
   return GSR_OK;
 }

@@ -58,16 +58,6 @@ __global__ void k_setup(ViewTable table, KWs ws, int64_t zlo, int64_t zcount, in
     for (int64_t k = gid; k < n; k += stride) ws.view_bits[k] = 0;
 }
 
-__global__ void k_fill_u32(uint32_t *p, uint32_t v, int64_t count) {
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < count; k += (int64_t)gridDim.x * blockDim.x)
-    p[k] = v;
-}
-
-__global__ void k_fill_f32(float *p, float v, int64_t count) {
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < count; k += (int64_t)gridDim.x * blockDim.x)
-    p[k] = v;
-}
-
 // ------------------------------------------------------------------ project
 
 __device__ __forceinline__ bool finite_params(const KParams &p, int64_t i) {
@@ -1004,21 +994,19 @@ __global__ __launch_bounds__(kScanThreads) void k_loss(KWs ws, int n_views, floa
 
 // -------------------------------------------------------------- project_bwd
 // Reverse mode of the projection for every view in which the Gaussian is
-// visible (view_only >= 0 restricts to one view and adds into the gradients).
+// visible.
 
 template <int D>
 __global__ __launch_bounds__(kBlock) void k_project_bwd(KParams p, const gsr_camera *cams, KOpts o, KWs ws,
-                                                        KGrads gr, float *stat_S, uint32_t *stat_n,
-                                                        int view_only) {
+                                                        KGrads gr, float *stat_S, uint32_t *stat_n) {
   constexpr int K = (D + 1) * (D + 1);
   __shared__ Cam64 s_cam[GSR_MAX_VIEWS];
   load_cams(s_cam, cams, ws.views, p.n_views, o);
   const int64_t n = p.n;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  uint32_t bits = ws.view_bits[i];
-  if (view_only >= 0) bits &= 1u << view_only;
-  const bool add = view_only >= 0 || o.accumulate;
+  const uint32_t bits = ws.view_bits[i];
+  const bool add = o.accumulate;
   if (bits == 0) {
     if (!add) {
       for (int a = 0; a < 3; a++) gr.means[a * n + i] = 0.f, gr.log_scales[a * n + i] = 0.f;
@@ -1313,16 +1301,6 @@ int launch_setup(const ViewTable &table, const KWs &ws, int64_t zlo, int64_t zco
   return last_err();
 }
 
-int launch_fill_u32(uint32_t *p, uint32_t value, int64_t count, void *stream) {
-  hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(count)), dim3(kBlock), 0, (hipStream_t)stream, p, value, count);
-  return last_err();
-}
-
-int launch_fill_f32(float *p, float value, int64_t count, void *stream) {
-  hipLaunchKernelGGL(k_fill_f32, dim3(grid_for(count)), dim3(kBlock), 0, (hipStream_t)stream, p, value, count);
-  return last_err();
-}
-
 // (the cameras of this step and of launch_visibility's are the set-up kernel's, in the workspace)
 int launch_project(const KParams &p, const gsr_camera *, const KOpts &o, const KWs &ws, int view_lo, int view_hi,
                    int or_bits, int table, void *stream) {
@@ -1381,15 +1359,16 @@ int launch_sort(const KWs &ws, int64_t tile_lo, int64_t tile_count, void *stream
   return last_err();
 }
 
+// (always all views of the workspace)
 int launch_project_bwd(const KParams &p, const gsr_camera *cams, const KOpts &o, const KWs &ws, const KGrads &g,
-                       float *stat_S, uint32_t *stat_n, int view_only, void *stream) {
+                       float *stat_S, uint32_t *stat_n, int, void *stream) {
   const dim3 grid(grid_for(p.n)), block(kBlock);
   hipStream_t s = (hipStream_t)stream;
   switch (p.sh_degree) {
-    case 0: hipLaunchKernelGGL(k_project_bwd<0>, grid, block, 0, s, p, cams, o, ws, g, stat_S, stat_n, view_only); break;
-    case 1: hipLaunchKernelGGL(k_project_bwd<1>, grid, block, 0, s, p, cams, o, ws, g, stat_S, stat_n, view_only); break;
-    case 2: hipLaunchKernelGGL(k_project_bwd<2>, grid, block, 0, s, p, cams, o, ws, g, stat_S, stat_n, view_only); break;
-    default: hipLaunchKernelGGL(k_project_bwd<3>, grid, block, 0, s, p, cams, o, ws, g, stat_S, stat_n, view_only); break;
+    case 0: hipLaunchKernelGGL(k_project_bwd<0>, grid, block, 0, s, p, cams, o, ws, g, stat_S, stat_n); break;
+    case 1: hipLaunchKernelGGL(k_project_bwd<1>, grid, block, 0, s, p, cams, o, ws, g, stat_S, stat_n); break;
+    case 2: hipLaunchKernelGGL(k_project_bwd<2>, grid, block, 0, s, p, cams, o, ws, g, stat_S, stat_n); break;
+    default: hipLaunchKernelGGL(k_project_bwd<3>, grid, block, 0, s, p, cams, o, ws, g, stat_S, stat_n); break;
   }
   return last_err();
 }
