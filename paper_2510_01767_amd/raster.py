@@ -122,6 +122,8 @@ class Rasterizer:
         self.ws_bytes = C.gsr_workspace_size(self.plan)
         self.ws = torch.empty(self.ws_bytes, dtype=torch.uint8, device=self.device)
         assert self.ws.data_ptr() % 256 == 0
+        # the workspace header's first two words: capacity exceeded, non-finite parameter
+        self._flags = self.ws[self.layout.header:self.layout.header + 8].view(torch.int32)
         self.pixels = sum(W * H for W, H in self.sizes)
         self.images = torch.empty(3 * self.pixels, dtype=torch.float32, device=self.device)
         self.loss = torch.zeros(1, dtype=torch.float32, device=self.device)
@@ -171,11 +173,12 @@ class Rasterizer:
         return C.gsr_workspace_layout(self.plan)
 
     # ------------------------------------------------------------ the calls
-    def step_l1(self, params, cams, targets, keep=None, stats=True, stream=None):
-        """gsr_forward_backward_l1: returns (loss [1], images [3P]); gradients land in self.grads."""
+    def step_l1(self, params, cams, targets, keep=None, stats=True, stream=None, grads=None):
+        """gsr_forward_backward_l1: returns (loss [1], images [3P]); gradients land in `grads`
+        (default: self.grads)."""
         self.generation += 1
         C.gsr_forward_backward_l1(self.plan, self.gaussians(params, keep), cams.data_ptr(), targets.data_ptr(),
-                                  self.images.data_ptr(), self.loss.data_ptr(), self.grads_struct(),
+                                  self.images.data_ptr(), self.loss.data_ptr(), self.grads_struct(grads),
                                   self.stats_struct(stats), self.ws.data_ptr(), self.ws_bytes,
                                   self.stream_handle(stream))
         return self.loss, self.images
@@ -220,6 +223,18 @@ class Rasterizer:
 
     def counts(self, stream=None, check=True) -> C.gsr_counts:
         return C.gsr_query_counts(self.plan, self.ws.data_ptr(), self.stream_handle(stream), check)
+
+    def check(self):
+        """Raises what counts() raises when the last step exceeded the capacity or met a
+        non-finite parameter; one synchronisation and eight bytes read, no counting."""
+        if any(self._flags.tolist()):
+            self.counts()
+
+    def fresh_grads(self):
+        """Gradient buffers for one call, or None where the plan adds to the ones it keeps."""
+        if self.options.accumulate_grads:
+            return None
+        return {k: torch.empty_like(v) for k, v in self.grads.items()}
 
     def autotune(self, params, cams, targets, reps=3, stream=None):
         self.generation += 1
@@ -299,9 +314,11 @@ class Rasterizer:
 
 class RasterizeL1Fn(torch.autograd.Function):
     """L1 training step as an autograd op: forward runs the fused
-    gsr_forward_backward_l1 and keeps its gradients (copies, so later calls
-    on the same Rasterizer do not change them); backward scales them by the
-    incoming gradient of the loss.  The images are a non-differentiable side
+    gsr_forward_backward_l1 and keeps its gradients (in buffers of its own,
+    so later calls on the same Rasterizer do not change them, and the
+    Rasterizer's own buffers are not written; a plan that accumulates
+    gradients keeps copies of those); backward scales them by the incoming
+    gradient of the loss.  The images are a non-differentiable side
     output.  The step's capacity and finiteness flags are checked before
     returning (one synchronisation): an overflowing step raises GsrError."""
 
@@ -309,9 +326,10 @@ class RasterizeL1Fn(torch.autograd.Function):
     def forward(ctx, means, log_scales, quats, opacity_logits, sh, rast: Rasterizer, cams, targets):
         params = dict(means=means.contiguous(), log_scales=log_scales.contiguous(), quats=quats.contiguous(),
                       opacity_logits=opacity_logits.contiguous(), sh=sh.contiguous())
-        loss, images = rast.step_l1(params, cams, targets)
-        rast.counts()
-        g = [rast.grads[k].clone() for k in PARAM_NAMES]
+        grads = rast.fresh_grads()
+        loss, images = rast.step_l1(params, cams, targets, grads=grads)
+        rast.check()
+        g = [rast.grads[k].clone() if grads is None else grads[k] for k in PARAM_NAMES]
         ctx.save_for_backward(*g)
         ctx.mark_non_differentiable(images)
         return loss.clone()[0], images.clone()
@@ -319,7 +337,9 @@ class RasterizeL1Fn(torch.autograd.Function):
     @staticmethod
     def backward(ctx, grad_loss, grad_images):
         g = ctx.saved_tensors
-        return tuple(x * grad_loss for x in g) + (None, None, None)
+        if torch.is_grad_enabled():
+            return tuple(x * grad_loss for x in g) + (None, None, None)
+        return tuple(torch._foreach_mul(list(g), grad_loss)) + (None, None, None)
 
 
 class StaleForwardError(RuntimeError):
@@ -337,14 +357,16 @@ class RasterizeFn(torch.autograd.Function):
     StaleForwardError if any call rewrote the workspace since, rather than
     returning gradients of another render.  One Rasterizer per render that
     must stay differentiable (or backward before the next render) avoids it.
-    The capacity and finiteness flags are checked before returning."""
+    The reverse pass writes gradient buffers of its own, not the
+    Rasterizer's, unless the plan accumulates gradients.  The capacity and
+    finiteness flags are checked before returning."""
 
     @staticmethod
     def forward(ctx, means, log_scales, quats, opacity_logits, sh, rast: Rasterizer, cams):
         params = dict(means=means.contiguous(), log_scales=log_scales.contiguous(), quats=quats.contiguous(),
                       opacity_logits=opacity_logits.contiguous(), sh=sh.contiguous())
         img = rast.forward(params, cams).clone()
-        rast.counts()
+        rast.check()
         ctx.rast, ctx.params, ctx.cams = rast, params, cams
         ctx.generation = rast.generation
         return img
@@ -356,8 +378,9 @@ class RasterizeFn(torch.autograd.Function):
             raise StaleForwardError("the Rasterizer's workspace was rewritten after this render's forward "
                                     f"(generation {ctx.generation} -> {rast.generation}); its reverse pass "
                                     "cannot run")
-        grads = rast.backward(ctx.params, ctx.cams, grad_images.contiguous())
-        return tuple(grads[k].clone() for k in PARAM_NAMES) + (None, None)
+        grads = rast.fresh_grads()
+        out = rast.backward(ctx.params, ctx.cams, grad_images.contiguous(), grads=grads)
+        return tuple(out[k].clone() if grads is None else out[k] for k in PARAM_NAMES) + (None, None)
 
 
 def render_l1(params, rast: Rasterizer, cams, targets):
