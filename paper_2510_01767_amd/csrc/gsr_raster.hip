@@ -108,6 +108,42 @@ __device__ __forceinline__ void load_batch(const KWs &ws, int64_t lo, int nb, Ld
   }
 }
 
+// The same in two halves, for launches with few tiles: the loads of a batch
+// into registers, its key's while the batch before it is culled and its
+// record's while that one is walked, then the registers into LDS.
+struct NextRec {
+  uint32_t idx;
+  float4 r0, r1, r2;
+  uint4 r3;
+};
+
+__device__ __forceinline__ void next_key(const KWs &ws, int64_t lo, int nb, NextRec &q) {
+  if ((int)threadIdx.x < nb) q.idx = (uint32_t)ws.keys[lo + threadIdx.x];
+}
+
+__device__ __forceinline__ void next_rec(const KWs &ws, int nb, NextRec &q) {
+  if ((int)threadIdx.x < nb) {
+    const float4 *rec = rec_ptr(ws, q.idx);
+    q.r0 = rec[0];
+    q.r1 = rec[1];
+    q.r2 = rec[2];
+    q.r3 = reinterpret_cast<const uint4 *>(rec)[3];
+  }
+}
+
+template <int B>
+__device__ __forceinline__ void store_next(const NextRec &q, int nb, LdsBatch<B> &s_rec, uint32_t *s_idx,
+                                           float *s_depth) {
+  if ((int)threadIdx.x < nb) {
+    s_rec.r0[threadIdx.x] = q.r0;
+    s_rec.r1[threadIdx.x] = q.r1;
+    s_rec.r2[threadIdx.x] = q.r2;
+    s_rec.reach[threadIdx.x] = __uint_as_float(q.r3.w);
+    if (s_idx) s_idx[threadIdx.x] = q.idx;
+    if (s_depth) s_depth[threadIdx.x] = __uint_as_float(q.r3.z);
+  }
+}
+
 // The kept entries of the batch for each of the wavefront's four
 // sub-blocks, in list order: an entry is tested against the strip's circle,
 // then each band of sub-blocks gets its interval and each sub-block two
@@ -158,7 +194,17 @@ struct Resident {
 // (the depth form of the blending sum, Sec. 3.2), from s_depth.  With COUNT
 // (profiling) it counts the pairs this lane evaluates after the culling and
 // the pairs it blends.
-template <int B, bool HIST, bool DEPTH = false, bool COUNT = false>
+//
+// FEW (launches with few tiles): four entries at a time, and the next batch's
+// loads in flight while this one is culled and walked.  With a wavefront or
+// two per SIMD nothing hides the latency of a step (list byte, record,
+// exponential) or of a batch (key, then record), so the four entries' list
+// bytes, records and alphas, which do not depend on one another, are in flight
+// together, and only the transmittance update goes entry by entry, in the same
+// order and with the same operations.
+constexpr int kAhead = 4;
+
+template <int B, bool HIST, bool FEW, bool DEPTH = false, bool COUNT = false>
 __device__ __forceinline__ void tile_forward(const KWs &ws, const KOpts &o, const TileCtx &c, LdsBatch<B> &s_rec,
                                              uint32_t *s_idx, uint8_t (*s_list)[4][B], float C[3], float &T,
                                              int &last, float *hist, Resident &res, float *s_depth = nullptr,
@@ -173,14 +219,27 @@ __device__ __forceinline__ void tile_forward(const KWs &ws, const KOpts &o, cons
   bool stopped = false;
   last = 0;
   res.nb = 0;
+  [[maybe_unused]] NextRec next = {};
+  if (FEW && c.start < c.end) {
+    const int nb = (int)min((int64_t)B, c.end - c.start);
+    next_key(ws, c.start, nb, next);
+    next_rec(ws, nb, next);
+  }
   for (int64_t b = c.start; b < c.end; b += B) {
     if (__syncthreads_and(done)) break;
     const int nb = (int)min((int64_t)B, c.end - b);
-    load_batch(ws, b, nb, s_rec, s_idx, DEPTH ? s_depth : nullptr);
+    const int nb_next = FEW ? (int)max((int64_t)0, min((int64_t)B, c.end - b - B)) : 0;
+    if constexpr (FEW) {
+      store_next(next, nb, s_rec, s_idx, DEPTH ? s_depth : nullptr);
+      next_key(ws, b + B, nb_next, next);
+    } else {
+      load_batch(ws, b, nb, s_rec, s_idx, DEPTH ? s_depth : nullptr);
+    }
     __syncthreads();
     int cq[4];
     const int cnt = sub_lists<B>(s_rec, nb, c, s_list[wave], cq);
     const int kmax = max(max(cq[0], cq[1]), max(cq[2], cq[3]));  // the same in every lane
+    if constexpr (FEW) next_rec(ws, nb_next, next);
     __syncthreads();
     res.lo = b;
     res.nb = nb;
@@ -189,7 +248,40 @@ __device__ __forceinline__ void tile_forward(const KWs &ws, const KOpts &o, cons
     const bool stopped_before = stopped;
     // each 16-lane row walks its own sub-block's list; a row whose list is
     // shorter idles (valid = false) while the others finish
-    for (int k = 0; k < kmax && !done; k++) {
+    if constexpr (FEW) {
+      for (int k0 = 0; k0 < kmax; k0 += kAhead) {
+        if (__ballot(!done) == 0ull) break;
+        const uint32_t bytes = *reinterpret_cast<const uint32_t *>(mine + k0);
+        int j[kAhead];
+        float4 r2[kAhead];
+        PairAlpha a[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; u++) {
+          j[u] = min((int)(bytes >> (8 * u) & 255u), nb - 1);
+          const LdsRec R = rec_at(s_rec, j[u]);
+          r2[u] = R.r2;
+          a[u] = pair_alpha<false>(pxc, pyc, R.r0, R.r1, amax);
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; u++) {
+          const bool valid = k0 + u < cnt && !done;
+          const bool hit = valid && a[u].in && a[u].alpha >= o.alpha_min;
+          const float Tn = T * (1.0f - a[u].alpha);
+          const bool stop = hit && Tn < o.T_min;
+          const bool take = hit && !stop;
+          const float w = take ? a[u].alpha * T : 0.0f;
+          C[0] = __fmaf_rn(w, r2[u].x, C[0]);
+          C[1] = __fmaf_rn(w, r2[u].y, C[1]);
+          C[2] = __fmaf_rn(w, r2[u].z, C[2]);
+          if (DEPTH) *D = __fmaf_rn(w, s_depth[j[u]], *D);
+          T = take ? Tn : T;
+          last = stop ? j[u] : last;
+          stopped = stopped || stop;
+          done = done || stop;
+        }
+      }
+    }
+    for (int k = 0; !FEW && k < kmax && !done; k++) {
       const bool valid = k < cnt;
       // past the row's count the list byte is stale and may name an entry the
       // batch did not load: clamped into the loaded entries (no branch), the
@@ -269,7 +361,10 @@ __device__ __forceinline__ float row_reduce_scatter(const float v[9], bool lb0, 
 // Batches are aligned like the forward's (c.start + k B), so when the
 // forward's last batch `res` is the first one needed here it is used as it
 // sits in LDS, culled lists included.
-template <int B, int RED, bool HIST>
+//   FEW (RED = 0): four entries at a time, as in the forward pass: their
+//            alphas and reciprocals together, the transmittance and suffix
+//            updates in order, then the four reductions together.
+template <int B, int RED, bool HIST, bool FEW>
 __device__ __forceinline__ void tile_backward(const KWs &ws, const KOpts &o, const TileCtx &c, LdsBatch<B> &s_rec,
                                               uint32_t *s_idx, uint8_t (*s_list)[4][B], float (*s_acc)[9],
                                               int *s_max, float T, int last, const float g[3],
@@ -292,9 +387,14 @@ __device__ __forceinline__ void tile_backward(const KWs &ws, const KOpts &o, con
   if (active && last > 0) atomicMax(s_max, last);
   __syncthreads();
   const int top = *s_max;  // entries [0, top) of the list can contribute
+  [[maybe_unused]] NextRec next = {};
+  [[maybe_unused]] bool loaded = false;
   for (int64_t lo = c.start + (int64_t)((top - 1) / B) * B; top > 0 && lo >= c.start; lo -= B) {
     const int nb_top = (int)min((int64_t)B, c.start + top - lo);
     int nb, cnt;
+    // the batch in front, loaded while this one is walked (all of its entries
+    // lie below `top`)
+    const int nb_next = FEW && lo > c.start ? B : 0;
     __syncthreads();
     if (res.nb > 0 && res.lo == lo) {
       // the forward's last batch, still in LDS with this wavefront's list
@@ -306,7 +406,8 @@ __device__ __forceinline__ void tile_backward(const KWs &ws, const KOpts &o, con
       __syncthreads();
     } else {
       nb = nb_top;
-      load_batch(ws, lo, nb, s_rec, s_idx);
+      if (FEW && loaded) store_next(next, nb, s_rec, s_idx, nullptr);
+      else load_batch(ws, lo, nb, s_rec, s_idx);
       if (RED >= 1)
         for (int e = threadIdx.x; e < nb * 9; e += blockDim.x) (&s_acc[0][0])[e] = 0.0f;
       __syncthreads();
@@ -314,13 +415,66 @@ __device__ __forceinline__ void tile_backward(const KWs &ws, const KOpts &o, con
       cnt = sub_lists<B>(s_rec, nb, c, s_list[wave], cq);
       __syncthreads();
     }
+    if constexpr (FEW) {
+      next_key(ws, lo - B, nb_next, next);
+      next_rec(ws, nb_next, next);
+      loaded = nb_next > 0;
+    }
     // entries at or past `top` contribute to no pixel
     const uint8_t *mine = s_list[wave][(lane & 63) >> 4];
     while (cnt > 0 && (int)mine[cnt - 1] >= nb_top) cnt--;
     int kmax = max(cnt, __shfl_xor(cnt, 16));  // the longest of the wavefront's four row lists
     kmax = __builtin_amdgcn_readfirstlane(max(kmax, __shfl_xor(kmax, 32)));  // uniform: a scalar loop counter
     const int jj_last = active ? last - (int)(lo - c.start) : 0;  // this pixel's entries: jj < jj_last
-    for (int k = kmax - 1; k >= 0; k--) {
+    if constexpr (FEW) {
+      static_assert(RED == 0 && !HIST, "the device-atomic form only");
+      for (int k0 = (kmax - 1) & ~(kAhead - 1); k0 >= 0; k0 -= kAhead) {
+        const uint32_t bytes = *reinterpret_cast<const uint32_t *>(mine + k0);
+        int jj[kAhead];
+        float4 r2[kAhead];
+        PairAlpha a[kAhead];
+        bool contrib[kAhead], any = false;
+#pragma unroll
+        for (int u = kAhead - 1; u >= 0; u--) {
+          jj[u] = min((int)(bytes >> (8 * u) & 255u), nb - 1);
+          const LdsRec R = rec_at(s_rec, jj[u]);
+          r2[u] = R.r2;
+          a[u] = pair_alpha<true>(pxc, pyc, R.r0, R.r1, amax);
+          contrib[u] = k0 + u < cnt && a[u].in && jj[u] < jj_last && a[u].alpha >= o.alpha_min;
+          any = any || contrib[u];
+        }
+        if (__ballot(any) == 0ull) continue;
+        float v[kAhead][9];
+#pragma unroll
+        for (int u = kAhead - 1; u >= 0; u--) {
+          const float al = contrib[u] ? a[u].alpha : 0.0f;
+          const float inv_om = __builtin_amdgcn_rcpf(1.0f - al);
+          const float Ti = T * inv_om, wgt = al * Ti;
+          const float gc = __fmaf_rn(g[2], r2[u].z, __fmaf_rn(g[1], r2[u].y, g[0] * r2[u].x));
+          const float dLda = __fmaf_rn(Ti, gc, -gS * inv_om);
+          gS = __fmaf_rn(wgt, gc, gS);
+          T = Ti;
+          const float dLdam = (contrib[u] && a[u].raw < o.alpha_max) ? dLda : 0.0f;
+          const float gp = dLdam * a[u].alpha;
+          const float gpx = gp * a[u].dx, gpy = gp * a[u].dy;
+          v[u][0] = gpx;
+          v[u][1] = gpy;
+          v[u][2] = gpx * a[u].dx;
+          v[u][3] = gpx * a[u].dy;
+          v[u][4] = gpy * a[u].dy;
+          v[u][5] = dLdam * a[u].G;
+          for (int ch = 0; ch < 3; ch++) v[u][6 + ch] = g[ch] * wgt;
+        }
+        float x[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; u++) x[u] = row_reduce_scatter(v[u], lb0, lb1, lb2, lb3);
+#pragma unroll
+        for (int u = kAhead - 1; u >= 0; u--)
+          if (k0 + u < cnt && comp_of_lane >= 0 && x[u] != 0.0f)
+            unsafeAtomicAdd(&ws.grad2d[(int64_t)s_idx[jj[u]] * kGrad2dStride + comp_of_lane], x[u]);
+      }
+    }
+    for (int k = FEW ? -1 : kmax - 1; k >= 0; k--) {
       const bool valid = k < cnt;
       const int jj = min((int)mine[k], nb - 1);  // as in the forward pass
       const int64_t j = lo + jj;
@@ -428,13 +582,13 @@ __device__ __forceinline__ float block_sum_fixed(float x, float *s_w) {
 
 // COUNT (profiling): pair_counts[p] = pairs blended into pixel p,
 // pair_counts[pixels_total + p] = pairs its lane evaluated.
-template <int TW, int TH, int B, bool HIST, bool DEPTH, bool COUNT>
+template <int TW, int TH, int B, bool HIST, bool DEPTH, bool COUNT, bool FEW>
 __global__ __launch_bounds__(kBlock) void k_raster_fwd(KWs ws, KOpts o, int64_t tile_lo, int64_t tile_count,
                                                        float *images, int n_views, float *depth,
                                                        uint32_t *pair_counts) {
   __shared__ LdsBatch<B> s_rec;
   __shared__ float s_depth[DEPTH ? B : 1];
-  __shared__ uint8_t s_list[4][4][B];  // [wavefront][sub-block][entry index in the batch]
+  alignas(16) __shared__ uint8_t s_list[4][4][B];  // [wavefront][sub-block][entry index in the batch]
   __shared__ ViewInfo s_views[GSR_MAX_VIEWS];
   for (int v = threadIdx.x; v < n_views; v += blockDim.x) s_views[v] = ws.views[v];
   __syncthreads();
@@ -447,7 +601,7 @@ __global__ __launch_bounds__(kBlock) void k_raster_fwd(KWs ws, KOpts o, int64_t 
   Resident res;
   float D = 0.0f;
   uint32_t n_eval = 0u, n_blend = 0u;
-  tile_forward<B, HIST, DEPTH, COUNT>(ws, o, c, s_rec, nullptr, s_list, C, T, last, ws.history, res, s_depth, &D,
+  tile_forward<B, HIST, FEW, DEPTH, COUNT>(ws, o, c, s_rec, nullptr, s_list, C, T, last, ws.history, res, s_depth, &D,
                                       &n_eval, &n_blend);
   if (c.inside) {
     const int64_t P = (int64_t)c.vi.W * c.vi.H;
@@ -492,12 +646,12 @@ __global__ __launch_bounds__(kBlock) void k_l1(KWs ws, KOpts o, int64_t tile_lo,
   if (threadIdx.x == 0) ws.tile_loss[t] = s;
 }
 
-template <int TW, int TH, int B, int RED, bool HIST>
+template <int TW, int TH, int B, int RED, bool HIST, bool FEW>
 __global__ __launch_bounds__(kBlock) void k_raster_bwd(KWs ws, KOpts o, int64_t tile_lo, int64_t tile_count,
                                                        const float *dLdC, int n_views) {
   __shared__ LdsBatch<B> s_rec;
   __shared__ uint32_t s_idx[B];
-  __shared__ uint8_t s_list[4][4][B];  // [wavefront][sub-block][entry index in the batch]
+  alignas(16) __shared__ uint8_t s_list[4][4][B];  // [wavefront][sub-block][entry index in the batch]
   __shared__ float s_acc[RED >= 1 ? B : 1][9];
   __shared__ int s_max;
   __shared__ ViewInfo s_views[GSR_MAX_VIEWS];
@@ -519,7 +673,7 @@ __global__ __launch_bounds__(kBlock) void k_raster_bwd(KWs ws, KOpts o, int64_t 
     T = ws.pix_T[c.vi.pix_base + c.pix];
     last = (int)ws.pix_last[c.vi.pix_base + c.pix];
   }
-  tile_backward<B, RED, HIST>(ws, o, c, s_rec, s_idx, s_list, s_acc, &s_max, T, last, g, ws.history,
+  tile_backward<B, RED, HIST, FEW>(ws, o, c, s_rec, s_idx, s_list, s_acc, &s_max, T, last, g, ws.history,
                               Resident{0, 0, 0});
 }
 
@@ -533,12 +687,12 @@ __global__ __launch_bounds__(kBlock) void k_raster_bwd(KWs ws, KOpts o, int64_t 
 // The reduce-scatter form (RED 0) is held to 64 VGPRs, eight wavefronts per
 // SIMD, which its LDS also allows (a few registers spill); the LDS
 // accumulator forms are limited by their LDS anyway.
-template <int TW, int TH, int B, int RED, bool HIST>
-__global__ __launch_bounds__(kBlock, RED == 0 && !HIST ? 8 : 1) void k_fused(KWs ws, KOpts o, const float *targets, float *images,
+template <int TW, int TH, int B, int RED, bool HIST, bool FEW>
+__global__ __launch_bounds__(kBlock, RED == 0 && !HIST && !FEW ? 8 : 1) void k_fused(KWs ws, KOpts o, const float *targets, float *images,
                                                   int n_views, const uint32_t *order) {
   __shared__ LdsBatch<B> s_rec;
   __shared__ uint32_t s_idx[B];
-  __shared__ uint8_t s_list[4][4][B];  // [wavefront][sub-block][entry index in the batch]
+  alignas(16) __shared__ uint8_t s_list[4][4][B];  // [wavefront][sub-block][entry index in the batch]
   __shared__ float s_acc[RED >= 1 ? B : 1][9];
   __shared__ int s_max;
   __shared__ float s_w[4];
@@ -559,7 +713,7 @@ __global__ __launch_bounds__(kBlock, RED == 0 && !HIST ? 8 : 1) void k_fused(KWs
     float C[3], T;
     int last;
     Resident res;
-    tile_forward<B, HIST>(ws, o, c, s_rec, s_idx, s_list, C, T, last, hist, res);
+    tile_forward<B, HIST, FEW>(ws, o, c, s_rec, s_idx, s_list, C, T, last, hist, res);
     float g[3] = {0.f, 0.f, 0.f};
     float acc = 0.0f;
     if (c.inside) {
@@ -578,7 +732,7 @@ __global__ __launch_bounds__(kBlock, RED == 0 && !HIST ? 8 : 1) void k_fused(KWs
     }
     const float s = block_sum_fixed(acc, s_w);
     if (threadIdx.x == 0) ws.tile_loss[t] = s;
-    tile_backward<B, RED, HIST>(ws, o, c, s_rec, s_idx, s_list, s_acc, &s_max, T, last, g, hist, res);
+    tile_backward<B, RED, HIST, FEW>(ws, o, c, s_rec, s_idx, s_list, s_acc, &s_max, T, last, g, hist, res);
   }
 }
 
@@ -660,16 +814,31 @@ int launch_tile_order(const KWs &ws, void *stream) {
     return last_err();                                                      \
   }
 
+// Launches of at most this many tiles leave a SIMD with few wavefronts, or
+// end on a few long lists: they take the kernels that walk four entries at a
+// time and load the next batch meanwhile (with 256-entry batches: the result
+// does not depend on them).  Larger ones keep eight wavefronts per SIMD busy,
+// and the registers that this takes cost more than the latency it hides.
+// Measured, one step's raster kernel without -> with: 20 000 Gaussians of a
+// unit cube at 128 to 1 024 pixels square (64 to 4 096 tiles) 356 -> 289, 172
+// -> 147, 140 -> 122 us; a block of 1 M at 1 024 square 134 -> 118 us; beyond
+// it one of four 1600 x 900 views (5 700 tiles) 102 + 209 -> 96 + 214 us, a
+// full-HD view (8 160) 50 + 107 -> 57 + 125 us, the 16-view block 4.82 -> 5.14
+// ms.
+constexpr int64_t kFewTiles = 4096;
+
 // reverse-pass kernels also select the reduction mode; the stored-history
 // variant always takes the row reduce-scatter (4)
-#define GSR_RED_CALL(KER, TW_, TH_, B_, ...)                                                           \
-  do {                                                                                               \
-    if (hist) hipLaunchKernelGGL((KER<TW_, TH_, B_, 4, true>), grid, block, 0, s, __VA_ARGS__);      \
-    else if (red == 4) hipLaunchKernelGGL((KER<TW_, TH_, B_, 4, false>), grid, block, 0, s, __VA_ARGS__); \
-    else if (red == 3) hipLaunchKernelGGL((KER<TW_, TH_, B_, 3, false>), grid, block, 0, s, __VA_ARGS__); \
-    else if (red == 2) hipLaunchKernelGGL((KER<TW_, TH_, B_, 2, false>), grid, block, 0, s, __VA_ARGS__); \
-    else if (red == 1) hipLaunchKernelGGL((KER<TW_, TH_, B_, 1, false>), grid, block, 0, s, __VA_ARGS__); \
-    else hipLaunchKernelGGL((KER<TW_, TH_, B_, 0, false>), grid, block, 0, s, __VA_ARGS__);               \
+#define GSR_RED_CALL(KER, TILES, TW_, TH_, B_, ...)                                                              \
+  do {                                                                                                           \
+    if (hist) hipLaunchKernelGGL((KER<TW_, TH_, B_, 4, true, false>), grid, block, 0, s, __VA_ARGS__);           \
+    else if (red == 4) hipLaunchKernelGGL((KER<TW_, TH_, B_, 4, false, false>), grid, block, 0, s, __VA_ARGS__); \
+    else if (red == 3) hipLaunchKernelGGL((KER<TW_, TH_, B_, 3, false, false>), grid, block, 0, s, __VA_ARGS__); \
+    else if (red == 2) hipLaunchKernelGGL((KER<TW_, TH_, B_, 2, false, false>), grid, block, 0, s, __VA_ARGS__); \
+    else if (red == 1) hipLaunchKernelGGL((KER<TW_, TH_, B_, 1, false, false>), grid, block, 0, s, __VA_ARGS__); \
+    else if ((TILES) <= kFewTiles)                                                                               \
+      hipLaunchKernelGGL((KER<TW_, TH_, 256, 0, false, true>), grid, block, 0, s, __VA_ARGS__);                  \
+    else hipLaunchKernelGGL((KER<TW_, TH_, B_, 0, false, false>), grid, block, 0, s, __VA_ARGS__);               \
   } while (0)
 
 int launch_raster_fwd(const KWs &ws, const KOpts &o, int64_t tile_lo, int64_t tile_count, float *images,
@@ -678,19 +847,26 @@ int launch_raster_fwd(const KWs &ws, const KOpts &o, int64_t tile_lo, int64_t ti
   if (tile_count <= 0) return 0;
   const dim3 grid((unsigned)xcd_grid(tile_count)), block(kBlock);
   hipStream_t s = (hipStream_t)stream;
+  const bool few = tile_count <= kFewTiles;
 #define CALL_FWD(a, b_, B)                                                                                        \
   do {                                                                                                              \
     if (pair_counts)                                                                                                \
-      hipLaunchKernelGGL((k_raster_fwd<a, b_, B, false, false, true>), grid, block, 0, s, ws, o, tile_lo,           \
+      hipLaunchKernelGGL((k_raster_fwd<a, b_, B, false, false, true, false>), grid, block, 0, s, ws, o, tile_lo,           \
+                         tile_count, images, n_views, depth, pair_counts);                                          \
+    else if (depth && few)                                                                                          \
+      hipLaunchKernelGGL((k_raster_fwd<a, b_, 256, false, true, false, true>), grid, block, 0, s, ws, o, tile_lo,     \
                          tile_count, images, n_views, depth, pair_counts);                                          \
     else if (depth)                                                                                                 \
-      hipLaunchKernelGGL((k_raster_fwd<a, b_, B, false, true, false>), grid, block, 0, s, ws, o, tile_lo,           \
+      hipLaunchKernelGGL((k_raster_fwd<a, b_, B, false, true, false, false>), grid, block, 0, s, ws, o, tile_lo,    \
                          tile_count, images, n_views, depth, pair_counts);                                          \
     else if (store_history)                                                                                         \
-      hipLaunchKernelGGL((k_raster_fwd<a, b_, B, true, false, false>), grid, block, 0, s, ws, o, tile_lo,           \
+      hipLaunchKernelGGL((k_raster_fwd<a, b_, B, true, false, false, false>), grid, block, 0, s, ws, o, tile_lo,           \
+                         tile_count, images, n_views, depth, pair_counts);                                          \
+    else if (few)                                                                                                   \
+      hipLaunchKernelGGL((k_raster_fwd<a, b_, 256, false, false, false, true>), grid, block, 0, s, ws, o, tile_lo,    \
                          tile_count, images, n_views, depth, pair_counts);                                          \
     else                                                                                                            \
-      hipLaunchKernelGGL((k_raster_fwd<a, b_, B, false, false, false>), grid, block, 0, s, ws, o, tile_lo,          \
+      hipLaunchKernelGGL((k_raster_fwd<a, b_, B, false, false, false, false>), grid, block, 0, s, ws, o, tile_lo,          \
                          tile_count, images, n_views, depth, pair_counts);                                          \
   } while (0)
   GSR_TILE_DISPATCH(16, 16, CALL_FWD)
@@ -714,7 +890,7 @@ int launch_raster_bwd(const KWs &ws, const KOpts &o, int64_t tile_lo, int64_t ti
   const dim3 grid((unsigned)xcd_grid(tile_count)), block(kBlock);
   hipStream_t s = (hipStream_t)stream;
   const bool hist = use_history != 0;
-#define CALL_BWD(a, b_, B) GSR_RED_CALL(k_raster_bwd, a, b_, B, ws, o, tile_lo, tile_count, dLdC, n_views)
+#define CALL_BWD(a, b_, B) GSR_RED_CALL(k_raster_bwd, tile_count, a, b_, B, ws, o, tile_lo, tile_count, dLdC, n_views)
   GSR_TILE_DISPATCH(16, 16, CALL_BWD)
   GSR_TILE_DISPATCH(32, 8, CALL_BWD)
   GSR_TILE_DISPATCH(8, 32, CALL_BWD)
@@ -729,7 +905,7 @@ int launch_fused(const KWs &ws, const KOpts &o, const float *targets, float *ima
   hipStream_t s = (hipStream_t)stream;
   const uint32_t *order = ws.tile_order;
   const bool hist = use_history != 0;
-#define CALL_FUSED(a, b_, B) GSR_RED_CALL(k_fused, a, b_, B, ws, o, targets, images, n_views, order)
+#define CALL_FUSED(a, b_, B) GSR_RED_CALL(k_fused, ws.tiles_total, a, b_, B, ws, o, targets, images, n_views, order)
   GSR_TILE_DISPATCH(16, 16, CALL_FUSED)
   GSR_TILE_DISPATCH(32, 8, CALL_FUSED)
   GSR_TILE_DISPATCH(8, 32, CALL_FUSED)
