@@ -9,6 +9,7 @@
 // recomputes each block's local offsets and writes every plane.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include "gsr_device.h"
@@ -20,7 +21,6 @@ namespace {
 
 constexpr int kItems = 4;                       // consecutive Gaussians per thread
 constexpr int kChunk = kBlock * kItems;         // Gaussians per workgroup
-constexpr int kPlaneSplit = 4;                  // workgroups sharing a chunk's planes
 
 struct Decision {
   int kind;  // 0 keep, 1 clone, 2 split
@@ -74,11 +74,11 @@ __device__ __forceinline__ uint64_t block_exclusive_sum(uint64_t x, uint64_t *s_
 
 __global__ __launch_bounds__(kBlock) void k_densify_count(KDensify k) {
   __shared__ uint64_t s_tmp[kBlock / 64];
-  const int64_t base = (int64_t)blockIdx.x * kChunk + (int64_t)threadIdx.x * kItems;
+  const int64_t base = (int64_t)blockIdx.x * kChunk + threadIdx.x;
   uint64_t sum = 0;
 #pragma unroll
   for (int j = 0; j < kItems; j++)
-    if (base + j < k.n) sum += (uint64_t)decide(k, base + j).c;
+    if (base + j * kBlock < k.n) sum += (uint64_t)decide(k, base + j * kBlock).c;
   uint64_t total;
   block_exclusive_sum(sum, s_tmp, &total);
   if (threadIdx.x == 0) k.block_sums[blockIdx.x] = total;
@@ -136,70 +136,116 @@ __device__ void child_means(const KDensify &k, int64_t i, int64_t pos) {
 
 enum PlaneMode { kMeans, kLogScales, kCopied, kMoments };
 
-// One plane of the block's Gaussians: consecutive lanes read consecutive
-// Gaussians and write their outputs, which are consecutive too; the
-// kItems loads of a thread are issued before its stores.  dec / pos: the
-// thread's Gaussians (threadIdx.x + r kBlock), c = 0 for none.
-template <int MODE>
-__device__ __forceinline__ void copy_plane(const KDensify &k, const int *dec, const int64_t *pos, const float *src,
-                                           float *dst) {
-  float v[kItems];
+struct Plane {
+  const float *src;
+  float *dst;
+  int mode;
+};
+
+// The planes of the outputs in order: the parameters', then each moment
+// plane's pair; thread u writes plane u's entry.
+__device__ __forceinline__ void list_planes(const KDensify &k, Plane *s_plane) {
+  const int params = 11 + k.sh_planes, u = threadIdx.x;
+  if (u >= params * (k.om[0] ? 3 : 1)) return;
+  const bool moment = u >= params, second = moment && ((u - params) & 1);
+  int p = moment ? (u - params) >> 1 : u;
+  const int rows[5] = {3, 3, 4, 1, k.sh_planes};
+  const float *const src[5] = {k.mean, k.ls, k.quat, k.opa, k.sh};
+  float *const dst[5] = {k.o_mean, k.o_ls, k.o_quat, k.o_opa, k.o_sh};
 #pragma unroll
-  for (int r = 0; r < kItems; r++) {
-    const bool load = (dec[r] & 3) != 0 && !(MODE == kMoments && (dec[r] >> 2) == 2);
-    v[r] = load ? src[threadIdx.x + r * kBlock] : 0.0f;
+  for (int g = 0; g < 5; g++) {
+    if (p >= 0 && p < rows[g]) {
+      const float *f = moment ? (second ? k.v[g] : k.m[g]) : src[g];
+      float *t = moment ? (second ? k.ov[g] : k.om[g]) : dst[g];
+      s_plane[u] = {f + p * k.n, t + p * k.n_out, moment ? kMoments : g == 0 ? kMeans : g == 1 ? kLogScales : kCopied};
+    }
+    p -= rows[g];
   }
+}
+
+__device__ __forceinline__ uint64_t uniform_u64(uint64_t x) {
+  return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32) |
+         (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+}
+
+// Entry u for the chunk from Gaussian `first` and output `bp` on, in scalar registers.
+__device__ __forceinline__ Plane plane_at(const Plane *s_plane, int u, int64_t first, int64_t bp) {
+  const Plane q = s_plane[u];
+  return {reinterpret_cast<const float *>(uniform_u64((uint64_t)q.src)) + first,
+          reinterpret_cast<float *>(uniform_u64((uint64_t)q.dst)) + bp, __builtin_amdgcn_readfirstlane(q.mode)};
+}
+
+// One plane of the block's Gaussians: consecutive lanes read consecutive
+// Gaussians and write their outputs, which are consecutive too.  dec: kind * 4
+// + outputs of the thread's Gaussians (threadIdx.x + r kBlock), 0 for none.
+__device__ __forceinline__ void load_plane(const Plane &p, const int *dec, float *v) {
+#pragma unroll
+  for (int r = 0; r < kItems; r++)
+    if ((dec[r] & 3) != 0) v[r] = p.src[threadIdx.x + r * kBlock];
+}
+
+__device__ __forceinline__ void store_plane(const Plane &p, const KDensify &k, const int *dec, const int *pos,
+                                            const float *v) {
 #pragma unroll
   for (int r = 0; r < kItems; r++) {
-    const int c = dec[r] & 3, kind = dec[r] >> 2;
-    // the children's means are written apart; a moment of a clone or a
-    // child starts from zero
-    const bool skip = MODE == kMeans && kind == 2;
-    const float x = (MODE == kLogScales && kind == 2) ? v[r] - k.child_dlog : v[r];
-    const float x1 = MODE == kMoments ? 0.0f : x;
-    if (c != 0 && !skip) dst[pos[r]] = x;
-    if (c == 2 && !skip) dst[pos[r] + 1] = x1;
+    const int c = dec[r] & 3;
+    const bool split = (dec[r] >> 2) == 2;
+    // the children's means are written apart; a moment of a clone or a child
+    // starts from zero
+    if (c == 0 || (p.mode == kMeans && split)) continue;
+    const float x = p.mode == kLogScales && split ? v[r] - k.child_dlog : p.mode == kMoments && split ? 0.0f : v[r];
+    p.dst[pos[r]] = x;
+    if (c == 2) p.dst[pos[r] + 1] = p.mode == kMoments ? 0.0f : x;
   }
 }
 
 // Decisions and block-local offsets first (kItems consecutive Gaussians per
-// thread, as in the count), kept in LDS; then plane by plane, each plane of
-// the block's Gaussians read and written in contiguous runs.
+// thread), kept in LDS; then plane by plane, each plane of the block's
+// Gaussians read and written in contiguous runs.  Bound by the bytes in
+// flight and HBM: 3 M Gaussians with moments, 4.4 GB in 1.11 ms (1.29 with
+// each plane's loads issued after the stores before them).
 __global__ __launch_bounds__(kBlock) void k_densify_apply(KDensify k) {
   __shared__ uint64_t s_tmp[kBlock / 64];
   __shared__ uint16_t s_off[kChunk];  // block-local output offset (< 2 kChunk)
   __shared__ uint8_t s_dec[kChunk];   // kind * 4 + c
+  __shared__ Plane s_plane[3 * (11 + 48)];
+  static_assert(3 * (11 + 48) <= kBlock, "one thread lists one plane");
+  list_planes(k, s_plane);
   const int64_t first = (int64_t)blockIdx.x * kChunk;
-  const int64_t base = first + (int64_t)threadIdx.x * kItems;
+  // (consecutive lanes decide consecutive Gaussians; the prefix then takes
+  // kItems consecutive ones per thread)
+#pragma unroll
+  for (int j = 0; j < kItems; j++) {
+    const int t = threadIdx.x + j * kBlock;
+    const Decision d = first + t < k.n ? decide(k, first + t) : Decision{0, 0};
+    s_dec[t] = (uint8_t)(d.kind * 4 + d.c);
+  }
+  __syncthreads();
   uint8_t dec[kItems];
   uint64_t sum = 0;
 #pragma unroll
   for (int j = 0; j < kItems; j++) {
-    const Decision d = base + j < k.n ? decide(k, base + j) : Decision{0, 0};
-    dec[j] = (uint8_t)(d.kind * 4 + d.c);
-    sum += (uint64_t)d.c;
+    dec[j] = s_dec[threadIdx.x * kItems + j];
+    sum += (uint64_t)(dec[j] & 3);
   }
   uint64_t total;
   uint64_t off = block_exclusive_sum(sum, s_tmp, &total);
 #pragma unroll
   for (int j = 0; j < kItems; j++) {
     s_off[threadIdx.x * kItems + j] = (uint16_t)off;
-    s_dec[threadIdx.x * kItems + j] = dec[j];
     off += dec[j] & 3;
   }
   __syncthreads();
-  const int64_t bp = (int64_t)k.block_sums[blockIdx.x];
+  const int64_t bp = (int64_t)uniform_u64(k.block_sums[blockIdx.x]);
   const int count = (int)min((int64_t)kChunk, k.n - first);
-  const int64_t n = k.n, no = k.n_out;
   // this thread's Gaussians for every plane, from LDS once
-  int mdec[kItems];
-  int64_t mpos[kItems];
+  int mdec[kItems], mpos[kItems];
 #pragma unroll
   for (int r = 0; r < kItems; r++) {
     const int t = threadIdx.x + r * kBlock;
     mdec[r] = t < count ? s_dec[t] : 0;
-    mpos[r] = t < count ? bp + s_off[t] : 0;
-    if (mpos[r] + (mdec[r] & 3) > no) mdec[r] = 0;  // fewer outputs than counted: the caller's n_out is short
+    mpos[r] = t < count ? s_off[t] : 0;
+    if (bp + mpos[r] + (mdec[r] & 3) > k.n_out) mdec[r] = 0;  // fewer outputs than counted: the caller's n_out is short
   }
   if (blockIdx.y == 0) {
 #pragma unroll
@@ -207,35 +253,33 @@ __global__ __launch_bounds__(kBlock) void k_densify_apply(KDensify k) {
       const int c = mdec[r] & 3;
       const int64_t i = first + threadIdx.x + r * kBlock;
       if (c == 0) continue;
-      if ((mdec[r] >> 2) == 2) child_means(k, i, mpos[r]);  // split Gaussians (a minority)
+      if ((mdec[r] >> 2) == 2) child_means(k, i, bp + mpos[r]);  // split Gaussians (a minority)
       if (k.parent) {
-        k.parent[mpos[r]] = i;
-        if (c == 2) k.parent[mpos[r] + 1] = i;
+        k.parent[bp + mpos[r]] = i;
+        if (c == 2) k.parent[bp + mpos[r] + 1] = i;
       }
     }
   }
-  // the planes, spread over the chunk's kPlaneSplit workgroups (plane number
-  // u of the parameters, then of each moment when present, goes to the
-  // workgroup u mod kPlaneSplit)
-  int u = 0;
-  const int y = blockIdx.y;
-  constexpr int G = kPlaneSplit;  // gridDim.y
-  for (int p = 0; p < 3; p++, u++)
-    if (u % G == y) copy_plane<kMeans>(k, mdec, mpos, k.mean + p * n + first, k.o_mean + p * no);
-  for (int p = 0; p < 3; p++, u++)
-    if (u % G == y) copy_plane<kLogScales>(k, mdec, mpos, k.ls + p * n + first, k.o_ls + p * no);
-  for (int p = 0; p < 4; p++, u++)
-    if (u % G == y) copy_plane<kCopied>(k, mdec, mpos, k.quat + p * n + first, k.o_quat + p * no);
-  if (u++ % G == y) copy_plane<kCopied>(k, mdec, mpos, k.opa + first, k.o_opa);
-  for (int p = 0; p < k.sh_planes; p++, u++)
-    if (u % G == y) copy_plane<kCopied>(k, mdec, mpos, k.sh + p * n + first, k.o_sh + p * no);
-  if (!k.om[0]) return;
-  const int rows[5] = {3, 3, 4, 1, k.sh_planes};
-  for (int g = 0; g < 5; g++)
-    for (int p = 0; p < rows[g]; p++) {
-      if (u++ % G == y) copy_plane<kMoments>(k, mdec, mpos, k.m[g] + p * n + first, k.om[g] + p * no);
-      if (u++ % G == y) copy_plane<kMoments>(k, mdec, mpos, k.v[g] + p * n + first, k.ov[g] + p * no);
+  // The planes, spread over the chunk's gridDim.y workgroups.  The next
+  // plane's loads are issued before this plane's stores: vector memory
+  // completes in order for a wavefront's wait, so loads issued after the
+  // stores would wait for them too.
+  const int planes = (11 + k.sh_planes) * (k.om[0] ? 3 : 1);
+  Plane cur = plane_at(s_plane, blockIdx.y, first, bp);
+  float v[kItems] = {}, w[kItems] = {};
+  load_plane(cur, mdec, v);
+  const int split = gridDim.y;
+  for (int u = blockIdx.y; u < planes; u += split) {
+    Plane next = cur;
+    if (u + split < planes) {
+      next = plane_at(s_plane, u + split, first, bp);
+      load_plane(next, mdec, w);
     }
+    store_plane(cur, k, mdec, mpos, v);
+    cur = next;
+#pragma unroll
+    for (int r = 0; r < kItems; r++) v[r] = w[r];
+  }
 }
 
 }  // namespace
@@ -252,10 +296,14 @@ int launch_densify_count(const KDensify &k, void *stream) {
 
 int launch_densify_apply(const KDensify &k, void *stream) {
   const int64_t nb = densify_blocks(k.n);
-  // each chunk's planes over kPlaneSplit workgroups: more loads in flight, at
-  // the price of deciding each Gaussian kPlaneSplit times
+  // Each chunk's planes over several workgroups, at the price of deciding each
+  // Gaussian as often: three where the chunks alone fill the chip (3 M
+  // Gaussians with moments 1.11 ms; 1.12 with two, 1.15 with four, 1.22 with
+  // eight), more where they do not, up to one a plane.
+  const int planes = (11 + k.sh_planes) * (k.om[0] ? 3 : 1);
+  const int64_t split = std::min<int64_t>(planes, std::max<int64_t>(3, 2048 / std::max<int64_t>(nb, 1)));
   if (nb > 0)
-    hipLaunchKernelGGL(k_densify_apply, dim3((unsigned)nb, kPlaneSplit), dim3(kBlock), 0, (hipStream_t)stream, k);
+    hipLaunchKernelGGL(k_densify_apply, dim3((unsigned)nb, (unsigned)split), dim3(kBlock), 0, (hipStream_t)stream, k);
   return last_err();
 }
 
