@@ -338,9 +338,10 @@ struct PairAlpha {
 // alpha >= alpha_min.  Below the record's pmin (ln(alpha_min / o) minus a
 // 5e-6 slack) o e^p stays under alpha_min by more than the rounding of the
 // float32 steps, so the alpha test alone rejects those pairs.  With
-// FINITE_G a positive exponent enters 2^x as 0, so that G (which the reverse
-// pass multiplies by zero on skipped pairs) stays finite; without it G and
-// raw may be infinite on skipped pairs, alpha is still at most alpha_max.
+// FINITE_G G is clamped to [0, 1] (the instruction's own modifier; a positive
+// exponent gives 1), so that G (which the reverse pass multiplies by zero on
+// skipped pairs) stays finite; without it G and raw may be infinite on skipped
+// pairs, alpha is still at most alpha_max.
 template <bool FINITE_G>
 __device__ __forceinline__ PairAlpha pair_alpha(float pxc, float pyc, const float4 &r0, const float4 &r1,
                                                 float alpha_max) {
@@ -350,7 +351,8 @@ __device__ __forceinline__ PairAlpha pair_alpha(float pxc, float pyc, const floa
   a.t = __fmaf_rn(r1.x, a.dx, r1.y * a.dy);
   a.cdy = r1.z * a.dy;
   const float p2 = __fmaf_rn(a.t, a.dx, a.cdy * a.dy);
-  a.G = __builtin_amdgcn_exp2f(FINITE_G ? fminf(p2, 0.0f) : p2);
+  const float G = __builtin_amdgcn_exp2f(p2);
+  a.G = FINITE_G ? __builtin_amdgcn_fmed3f(G, 0.0f, 1.0f) : G;
   a.in = !(p2 > 0.0f);
   a.raw = r1.w * a.G;
   // min(raw, alpha_max) as a signed integer minimum of the bit patterns:
