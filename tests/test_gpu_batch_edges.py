@@ -12,6 +12,7 @@ from paper_2510_01767_amd import gsr as C
 from paper_2510_01767_amd import scenes
 from paper_2510_01767_amd.raster import Rasterizer, camera_tensor, pack_images, scene_tensors
 from tests import parity
+from tests.test_gpu_fcs import compare_depth, unpack_depth
 
 pytestmark = pytest.mark.gpu
 
@@ -65,3 +66,18 @@ def test_many_tiles(tile, batch, n):
     # 32-bit atomic additions, which no bound per element relative to the group
     # covers (it varies from run to run with their order); the group's does.
     check(n, LARGE, tile, batch, 0, False, "plain", elementwise=False)
+
+
+@pytest.mark.parametrize("sizes", [SMALL, LARGE])
+@pytest.mark.parametrize("batch,n", [(64, 64), (128, 200), (256, 300)])
+def test_depth(sizes, batch, n):
+    C.load(build_if_missing=False)
+    print("[gpu-case] batch edges depth", n, sizes, batch, flush=True)
+    scene = scenes.small_ragged(seed=scenes.SEED_BASE + n, n=n, sh_degree=0, sizes=sizes)
+    scene.opacity_logits[:] = scene.opacity_logits * 0.3
+    wh = [(c["W"], c["H"]) for c in scene.cameras]
+    r = Rasterizer(n, 0, wh, mode="batched", lds_batch=batch)
+    _, depth = r.render_depth(scene_tensors(scene), camera_tensor(scene.cameras))
+    torch.cuda.synchronize()
+    ora = oracle.forward(oracle.Params.from_scene(scene), scene.cameras, parity.opts_for())
+    compare_depth(unpack_depth(depth, wh), ora)
