@@ -93,7 +93,7 @@ typedef struct gsr_options {
   int32_t tile_w;        /* 16x16, 32x8 or 8x32 (width x height), 256 pixels */
   int32_t tile_h;
   int32_t bwd_variant;   /* GSR_BWD_* */
-  int32_t lds_batch;     /* list entries staged in LDS per round: 64, 128 or 256 */
+  int32_t lds_batch;     /* places for list entries in LDS per round: 64, 128 or 256 (one stays free) */
   int32_t grid_per_cu;   /* persistent raster grid = grid_per_cu * compute units (1..32) */
   int32_t accumulate_grads; /* 0: gradients are overwritten; 1: added to */
   int32_t check_finite;  /* 1: flag non-finite parameters (GSR_ERR_NONFINITE via query) */
