@@ -169,7 +169,8 @@ typedef struct gsr_counts {
  * gp dy^2, with p = -d^T Q d / 2 the exponent of the Gaussian's alpha), then
  * dL/dopacity and dL/dcolour (3); its 2D gradient is dL/dmean2d = Q (m0, m1),
  * dL/d(A, B, C) = -(m2 / 2, m3, m4 / 2).  Then its in-tile ranks (4 x u32),
- * tile rectangle (2 x u32) and depth bits. */
+ * tile rectangle (2 x u32) and depth bits.  A spare slot follows the last
+ * record's. */
 #define GSR_SLOT_FLOATS 16
 typedef struct gsr_layout {
   size_t header, view_table, view_bits, records, grad2d, tile_count, tile_start, tile_fill,

@@ -90,7 +90,8 @@ void compute_layout(gsr_plan &p) {
   take(L.view_table, sizeof(ViewInfo) * GSR_MAX_VIEWS);
   take(L.view_bits, sizeof(uint32_t) * (size_t)n);
   take(L.records, sizeof(float) * 16 * (size_t)L.vn);
-  take(L.grad2d, sizeof(float) * kGrad2dStride * (size_t)L.vn);
+  // (a spare slot behind the records': what the reverse raster adds for the padding of its lists)
+  take(L.grad2d, sizeof(float) * kGrad2dStride * (size_t)(L.vn + 1));
   take(L.tile_count, sizeof(uint32_t) * (size_t)tmax);
   take(L.tile_start, sizeof(uint32_t) * (size_t)(tmax + 1));
   take(L.tile_fill, sizeof(uint32_t) * (size_t)tmax);

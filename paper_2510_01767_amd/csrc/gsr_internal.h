@@ -115,6 +115,7 @@ constexpr int kRecordFloat4 = 4;
 //   [13, 15) tile rectangle (x0 | y0 << 16, x1 | y1 << 16)
 //   [15]     depth (camera z, float bits: the sort key's high word)
 // The projection writes the slot whole; the scatter reads its upper half.
+// One more slot follows the records': nothing reads it (the raster's list padding adds to it).
 constexpr int kGrad2dStride = GSR_SLOT_FLOATS;
 
 struct KWs {
@@ -122,7 +123,7 @@ struct KWs {
   ViewInfo *views;
   uint32_t *view_bits;
   float *records;   // [vn][16]
-  float *grad2d;    // [vn][16] record slots
+  float *grad2d;    // [vn + 1][16] record slots
   uint32_t *tile_count, *tile_start, *tile_fill;
   float *tile_loss;
   uint32_t *tile_order;

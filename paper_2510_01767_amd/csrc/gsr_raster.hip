@@ -80,7 +80,9 @@ __device__ __forceinline__ void tile_ctx(const KWs &ws, const ViewInfo *views, i
 // the record's index.  A batch has at most B - 1 entries; the last place is
 // kNone, an entry whose alpha is 0 at every pixel, which fills up the shorter
 // lists of a wavefront's four sub-blocks: no step of a walk then asks whether
-// its row still has an entry.  (With that, the stop kept as lane masks and the
+// its row still has an entry.  Its record index is the spare slot behind the
+// records': the reverse walk's products with its alpha of 0 are NaN where the
+// image gradient is infinite or NaN, and a NaN is added somewhere.  (With that, the stop kept as lane masks and the
 // banked reduction below, a walk takes 25 vector operations an entry forward
 // and 66 in reverse.  The fused kernel before -> with them, a city of 8 M
 // Gaussians in 32 full-HD views 7.65 -> 7.20 ms, a cloud of 20 M in 8 views of
@@ -94,11 +96,12 @@ struct LdsBatch {
 };
 
 template <int B>
-__device__ __forceinline__ void init_none(LdsBatch<B> &s, float *s_depth = nullptr) {
+__device__ __forceinline__ void init_none(LdsBatch<B> &s, const KWs &ws, float *s_depth = nullptr) {
   if (threadIdx.x == 0) {
     if (s_depth) s_depth[LdsBatch<B>::kNone] = 0.0f;
     constexpr int e = LdsBatch<B>::kNone;
-    s.r0[e] = s.r1[e] = s.r2[e] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    s.r0[e] = s.r1[e] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    s.r2[e] = make_float4(0.0f, 0.0f, 0.0f, __uint_as_float((uint32_t)ws.vn));
     s.cull[e] = make_float2(-1.0f, 0.0f);
   }
 }
@@ -626,7 +629,7 @@ __global__ __launch_bounds__(kBlock) void k_raster_fwd(KWs ws, KOpts o, int64_t 
   alignas(16) __shared__ uint8_t s_list[4][4][B];  // [wavefront][sub-block][entry index in the batch]
   __shared__ ViewInfo s_views[GSR_MAX_VIEWS];
   for (int v = threadIdx.x; v < n_views; v += blockDim.x) s_views[v] = ws.views[v];
-  init_none(s_rec, DEPTH ? s_depth : nullptr);
+  init_none(s_rec, ws, DEPTH ? s_depth : nullptr);
   __syncthreads();
   const int64_t b = xcd_remap(blockIdx.x, tile_count);
   if (b >= tile_count) return;
@@ -691,7 +694,7 @@ __global__ __launch_bounds__(kBlock) void k_raster_bwd(KWs ws, KOpts o, int64_t 
   __shared__ int s_max;
   __shared__ ViewInfo s_views[GSR_MAX_VIEWS];
   for (int v = threadIdx.x; v < n_views; v += blockDim.x) s_views[v] = ws.views[v];
-  init_none(s_rec);
+  init_none(s_rec, ws);
   __syncthreads();
   const int64_t b = xcd_remap(blockIdx.x, tile_count);
   if (b >= tile_count) return;
@@ -734,7 +737,7 @@ __global__ __launch_bounds__(kBlock, RED == 0 && !HIST && !FEW ? 8 : 1) void k_f
   __shared__ int64_t s_item;
   __shared__ ViewInfo s_views[GSR_MAX_VIEWS];
   for (int v = threadIdx.x; v < n_views; v += blockDim.x) s_views[v] = ws.views[v];
-  init_none(s_rec);
+  init_none(s_rec, ws);
   float *hist = ws.history;
   const int cls = (int)(blockIdx.x & 7u);
   for (;;) {
