@@ -1,7 +1,9 @@
 """An image gradient with a NaN and an infinity in it, as a caller's own loss can
 give: only Gaussians that the pixel's tile lists take part in that pixel, so
 every other gradient equals the run in which those pixels have none, with
-sub-block lists of unequal lengths, on images of few and of many tiles."""
+sub-block lists of unequal lengths, on images of few and of many tiles.  An
+entry that no pixel of a wavefront's step blends is left out of the reverse
+walk, whichever walk that is."""
 import numpy as np
 import pytest
 import torch
@@ -18,13 +20,13 @@ MANY = ((70, 61), (1040, 1024))  # more than 4096 tiles
 RTOL = 1e-5  # the order of float atomics
 
 
-def build(n, sizes, tile, reduce, seed=0):
+def build(n, sizes, tile, reduce, **kw):
     C.load(build_if_missing=False)
-    scene = scenes.small_ragged(seed=scenes.SEED_BASE + n + seed, n=n, sh_degree=1, sizes=sizes)
+    scene = scenes.small_ragged(seed=scenes.SEED_BASE + n, n=n, sh_degree=1, sizes=sizes)
     if sizes is MANY:
         scene.log_scales += 1.5
     r = Rasterizer(n, 1, [(c["W"], c["H"]) for c in scene.cameras], mode="batched", tile=tile, bwd_reduce=reduce,
-                   capacity=1 << 21)
+                   capacity=1 << 21, **kw)
     return scene, r, scene_tensors(scene), camera_tensor(scene.cameras)
 
 
@@ -84,3 +86,26 @@ def test_only_listed_gaussians_take_part(sizes, tile, reduce):
         assert bool(torch.isfinite(a).all()), k
         assert float(torch.linalg.norm(a - b)) <= RTOL * float(torch.linalg.norm(b)), k
     assert not bool(torch.isfinite(got["sh"]).all())  # those that the pixels blend carry it
+
+
+@pytest.mark.parametrize("what", ["image gradient", "colour"])
+@pytest.mark.parametrize("tile", [(16, 16), (32, 8), (8, 32)])
+@pytest.mark.parametrize("n", [150, 900])
+def test_few_tiles_touch_what_many_tiles_do(n, tile, what):
+    """The walk by four entries (reduction 0, few tiles) adds a non-finite term to no Gaussian that the walk by one
+    (reduction 4) leaves out: an entry that no pixel of its step blends.  For an image gradient they are the same."""
+    print("[gpu-case] non-finite", what, n, tile, flush=True)
+    touched = []
+    for reduce in (0, 4):
+        scene, r, params, cams = build(n, FEW, tile, reduce, lds_batch=256)
+        params["opacity_logits"] += 2.0  # many pixels stop before their list's end
+        g = torch.from_numpy(np.random.default_rng(n).uniform(-1.0, 1.0, 3 * r.pixels).astype(np.float32)).cuda()
+        if what == "colour":
+            params["sh"][0, ::50] = float("inf")
+        else:
+            g = odd_pixels(r, g, 1, 17)[0]
+        touched.append({k: ~torch.isfinite(v) for k, v in gradients(r, params, cams, g).items()})
+    assert 0 < int(touched[1]["opacity_logits"].sum()) < n
+    for k in touched[0]:
+        assert not bool((touched[0][k] & ~touched[1][k]).any()), k
+        assert what == "colour" or torch.equal(touched[0][k], touched[1][k]), k
