@@ -296,9 +296,10 @@ __device__ __forceinline__ void tile_forward(const KWs &ws, const KOpts &o, cons
           const bool stop = hit && Tn < o.T_min;
           const bool take = hit && !stop;
           const float w = take ? a[u].alpha * T : 0.0f;
-          C[0] = __fmaf_rn(w, r2[u].x, C[0]);
-          C[1] = __fmaf_rn(w, r2[u].y, C[1]);
-          C[2] = __fmaf_rn(w, r2[u].z, C[2]);
+          // (a stopped lane does not take 0 times an infinite colour either)
+          C[0] = done ? C[0] : __fmaf_rn(w, r2[u].x, C[0]);
+          C[1] = done ? C[1] : __fmaf_rn(w, r2[u].y, C[1]);
+          C[2] = done ? C[2] : __fmaf_rn(w, r2[u].z, C[2]);
           if (DEPTH) *D = __fmaf_rn(w, s_depth[j[u]], *D);
           T = take ? Tn : T;
           last = stop ? j[u] : last;
