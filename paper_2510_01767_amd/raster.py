@@ -336,10 +336,8 @@ class RasterizeL1Fn(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, grad_loss, grad_images):
-        g = ctx.saved_tensors
-        if torch.is_grad_enabled():
-            return tuple(x * grad_loss for x in g) + (None, None, None)
-        return tuple(torch._foreach_mul(list(g), grad_loss)) + (None, None, None)
+        # (not torch._foreach_mul: it has no batching rule, is_grads_batched would fail)
+        return tuple(x * grad_loss for x in ctx.saved_tensors) + (None, None, None)
 
 
 class StaleForwardError(RuntimeError):
