@@ -230,12 +230,6 @@ class Rasterizer:
         if any(self._flags.tolist()):
             self.counts()
 
-    def fresh_grads(self):
-        """Gradient buffers for one call, or None where the plan adds to the ones it keeps."""
-        if self.options.accumulate_grads:
-            return None
-        return {k: torch.empty_like(v) for k, v in self.grads.items()}
-
     def autotune(self, params, cams, targets, reps=3, stream=None):
         self.generation += 1
         best, ms = C.gsr_autotune(self.plan, self.gaussians(params), cams.data_ptr(), targets.data_ptr(),
@@ -314,11 +308,10 @@ class Rasterizer:
 
 class RasterizeL1Fn(torch.autograd.Function):
     """L1 training step as an autograd op: forward runs the fused
-    gsr_forward_backward_l1 and keeps its gradients (in buffers of its own,
-    so later calls on the same Rasterizer do not change them, and the
-    Rasterizer's own buffers are not written; a plan that accumulates
-    gradients keeps copies of those); backward scales them by the incoming
-    gradient of the loss.  The images are a non-differentiable side
+    gsr_forward_backward_l1 and keeps copies of its gradients (so later calls
+    on the same Rasterizer do not change them; the Rasterizer's own planes hold
+    the step's gradients too, as after step_l1); backward scales them by the
+    incoming gradient of the loss.  The images are a non-differentiable side
     output.  The step's capacity and finiteness flags are checked before
     returning (one synchronisation): an overflowing step raises GsrError."""
 
@@ -326,11 +319,9 @@ class RasterizeL1Fn(torch.autograd.Function):
     def forward(ctx, means, log_scales, quats, opacity_logits, sh, rast: Rasterizer, cams, targets):
         params = dict(means=means.contiguous(), log_scales=log_scales.contiguous(), quats=quats.contiguous(),
                       opacity_logits=opacity_logits.contiguous(), sh=sh.contiguous())
-        grads = rast.fresh_grads()
-        loss, images = rast.step_l1(params, cams, targets, grads=grads)
+        loss, images = rast.step_l1(params, cams, targets)
         rast.check()
-        g = [rast.grads[k].clone() if grads is None else grads[k] for k in PARAM_NAMES]
-        ctx.save_for_backward(*g)
+        ctx.save_for_backward(*[rast.grads[k].clone() for k in PARAM_NAMES])
         ctx.mark_non_differentiable(images)
         return loss.clone()[0], images.clone()
 
@@ -355,9 +346,9 @@ class RasterizeFn(torch.autograd.Function):
     StaleForwardError if any call rewrote the workspace since, rather than
     returning gradients of another render.  One Rasterizer per render that
     must stay differentiable (or backward before the next render) avoids it.
-    The reverse pass writes gradient buffers of its own, not the
-    Rasterizer's, unless the plan accumulates gradients.  The capacity and
-    finiteness flags are checked before returning."""
+    The reverse pass leaves its gradients in the Rasterizer's planes, as
+    Rasterizer.backward does, and returns copies.  The capacity and finiteness
+    flags are checked before returning."""
 
     @staticmethod
     def forward(ctx, means, log_scales, quats, opacity_logits, sh, rast: Rasterizer, cams):
@@ -376,9 +367,8 @@ class RasterizeFn(torch.autograd.Function):
             raise StaleForwardError("the Rasterizer's workspace was rewritten after this render's forward "
                                     f"(generation {ctx.generation} -> {rast.generation}); its reverse pass "
                                     "cannot run")
-        grads = rast.fresh_grads()
-        out = rast.backward(ctx.params, ctx.cams, grad_images.contiguous(), grads=grads)
-        return tuple(out[k].clone() if grads is None else out[k] for k in PARAM_NAMES) + (None, None)
+        grads = rast.backward(ctx.params, ctx.cams, grad_images.contiguous())
+        return tuple(grads[k].clone() for k in PARAM_NAMES) + (None, None)
 
 
 def render_l1(params, rast: Rasterizer, cams, targets):
