@@ -93,7 +93,10 @@ typedef struct gsr_options {
   int32_t tile_w;        /* 16x16, 32x8 or 8x32 (width x height), 256 pixels */
   int32_t tile_h;
   int32_t bwd_variant;   /* GSR_BWD_* */
-  int32_t lds_batch;     /* places for list entries in LDS per round: 64, 128 or 256 (one stays free) */
+  int32_t lds_batch;     /* places for list entries in LDS per round: 64, 128 or 256 (one stays free).
+                            Launches of at most 4096 tiles take 256 whatever is set here (the forward
+                            render without stored history; the reverse pass and the fused step with
+                            the recompute variant and bwd_reduce 0): results do not depend on it */
   int32_t grid_per_cu;   /* persistent raster grid = grid_per_cu * compute units (1..32) */
   int32_t accumulate_grads; /* 0: gradients are overwritten; 1: added to */
   int32_t check_finite;  /* 1: flag non-finite parameters (GSR_ERR_NONFINITE via query) */
@@ -159,7 +162,7 @@ typedef struct gsr_counts {
   int64_t visible_union; /* Gaussians visible in at least one view */
   int32_t overflow;      /* 1 when capacity_intersections was exceeded */
   int32_t nonfinite;     /* 1 when check_finite found a non-finite parameter */
-  int32_t tile_w, tile_h, bwd_variant, lds_batch, grid_per_cu, mode;
+  int32_t tile_w, tile_h, bwd_variant, lds_batch, grid_per_cu, mode; /* lds_batch as set in the plan */
 } gsr_counts;
 
 /* Internal byte offsets of the workspace (for tests and profiling).  grad2d
@@ -278,7 +281,8 @@ gsr_status gsr_query_counts(gsr_plan *plan, const void *ws, gsr_counts *counts, 
 
 /* Times the batched fused step for each candidate (tile shape 16x16, 32x8,
  * 8x32; lds_batch; grid_per_cu; backward variant within the history budget;
- * reverse reduction 0, 2, 3, 4) with device events, `reps` steps each after
+ * reverse reduction 0, 2, 3, 4; of the batch sizes only 256 where lds_batch
+ * has no effect) with device events, `reps` steps each after
  * one warm-up step, a candidate scoring its fastest step; the three fastest
  * are timed again over 2 reps + 3 steps, then the fastest of those with the
  * other project_table setting; the fastest is stored in the plan.  Steps

@@ -820,6 +820,9 @@ gsr_status gsr_autotune(gsr_plan *plan, const gsr_gaussians *g, const gsr_camera
             plan->opt = o;
             compute_layout(*plan);
             if (var == GSR_BWD_STORED && plan->layout.history_entries == 0) continue;
+            // (the few-tile kernels take one batch size: the others would be the same step again)
+            if (var == GSR_BWD_RECOMPUTE && red == 0 && b != kFewTilesBatch && plan->layout.tiles_total <= kFewTiles)
+              continue;
             float ms = 0.f;
             s = time_candidate(o, reps, ms);
             if (s != GSR_OK) break;

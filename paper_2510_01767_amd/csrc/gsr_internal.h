@@ -136,6 +136,20 @@ struct KWs {
   int64_t n_views;
 };
 
+// Launches of at most this many tiles leave a SIMD with few wavefronts, or
+// end on a few long lists: they take the kernels that walk four entries at a
+// time and load the next batch meanwhile (with 256-entry batches: the result
+// does not depend on them).  Larger ones keep eight wavefronts per SIMD busy,
+// and the registers that this takes cost more than the latency it hides.
+// Measured, one step's raster kernel without -> with: 20 000 Gaussians of a
+// unit cube at 128 to 1 024 pixels square (64 to 4 096 tiles) 356 -> 289, 172
+// -> 147, 140 -> 122 us; a block of 1 M at 1 024 square 134 -> 118 us; beyond
+// it one of four 1600 x 900 views (5 700 tiles) 102 + 209 -> 96 + 214 us, a
+// full-HD view (8 160) 50 + 107 -> 57 + 125 us, the 16-view block 4.82 -> 5.14
+// ms.
+constexpr int64_t kFewTiles = 4096;
+constexpr int kFewTilesBatch = 256;
+
 // ---------------------------------------------------------------- launchers
 // Defined in gsr_kernels.hip; every launcher enqueues on `stream` and returns
 // the launch's hipError_t as int.

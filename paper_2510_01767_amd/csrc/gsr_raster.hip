@@ -861,19 +861,6 @@ int launch_tile_order(const KWs &ws, void *stream) {
     return last_err();                                                      \
   }
 
-// Launches of at most this many tiles leave a SIMD with few wavefronts, or
-// end on a few long lists: they take the kernels that walk four entries at a
-// time and load the next batch meanwhile (with 256-entry batches: the result
-// does not depend on them).  Larger ones keep eight wavefronts per SIMD busy,
-// and the registers that this takes cost more than the latency it hides.
-// Measured, one step's raster kernel without -> with: 20 000 Gaussians of a
-// unit cube at 128 to 1 024 pixels square (64 to 4 096 tiles) 356 -> 289, 172
-// -> 147, 140 -> 122 us; a block of 1 M at 1 024 square 134 -> 118 us; beyond
-// it one of four 1600 x 900 views (5 700 tiles) 102 + 209 -> 96 + 214 us, a
-// full-HD view (8 160) 50 + 107 -> 57 + 125 us, the 16-view block 4.82 -> 5.14
-// ms.
-constexpr int64_t kFewTiles = 4096;
-
 // reverse-pass kernels also select the reduction mode; the stored-history
 // variant always takes the row reduce-scatter (4)
 #define GSR_RED_CALL(KER, TILES, TW_, TH_, B_, ...)                                                              \
@@ -884,7 +871,7 @@ constexpr int64_t kFewTiles = 4096;
     else if (red == 2) hipLaunchKernelGGL((KER<TW_, TH_, B_, 2, false, false>), grid, block, 0, s, __VA_ARGS__); \
     else if (red == 1) hipLaunchKernelGGL((KER<TW_, TH_, B_, 1, false, false>), grid, block, 0, s, __VA_ARGS__); \
     else if ((TILES) <= kFewTiles)                                                                               \
-      hipLaunchKernelGGL((KER<TW_, TH_, 256, 0, false, true>), grid, block, 0, s, __VA_ARGS__);                  \
+      hipLaunchKernelGGL((KER<TW_, TH_, kFewTilesBatch, 0, false, true>), grid, block, 0, s, __VA_ARGS__);                  \
     else hipLaunchKernelGGL((KER<TW_, TH_, B_, 0, false, false>), grid, block, 0, s, __VA_ARGS__);               \
   } while (0)
 
@@ -901,7 +888,7 @@ int launch_raster_fwd(const KWs &ws, const KOpts &o, int64_t tile_lo, int64_t ti
       hipLaunchKernelGGL((k_raster_fwd<a, b_, B, false, false, true, false>), grid, block, 0, s, ws, o, tile_lo,           \
                          tile_count, images, n_views, depth, pair_counts);                                          \
     else if (depth && few)                                                                                          \
-      hipLaunchKernelGGL((k_raster_fwd<a, b_, 256, false, true, false, true>), grid, block, 0, s, ws, o, tile_lo,     \
+      hipLaunchKernelGGL((k_raster_fwd<a, b_, kFewTilesBatch, false, true, false, true>), grid, block, 0, s, ws, o, tile_lo,     \
                          tile_count, images, n_views, depth, pair_counts);                                          \
     else if (depth)                                                                                                 \
       hipLaunchKernelGGL((k_raster_fwd<a, b_, B, false, true, false, false>), grid, block, 0, s, ws, o, tile_lo,    \
@@ -910,7 +897,7 @@ int launch_raster_fwd(const KWs &ws, const KOpts &o, int64_t tile_lo, int64_t ti
       hipLaunchKernelGGL((k_raster_fwd<a, b_, B, true, false, false, false>), grid, block, 0, s, ws, o, tile_lo,           \
                          tile_count, images, n_views, depth, pair_counts);                                          \
     else if (few)                                                                                                   \
-      hipLaunchKernelGGL((k_raster_fwd<a, b_, 256, false, false, false, true>), grid, block, 0, s, ws, o, tile_lo,    \
+      hipLaunchKernelGGL((k_raster_fwd<a, b_, kFewTilesBatch, false, false, false, true>), grid, block, 0, s, ws, o, tile_lo,    \
                          tile_count, images, n_views, depth, pair_counts);                                          \
     else                                                                                                            \
       hipLaunchKernelGGL((k_raster_fwd<a, b_, B, false, false, false, false>), grid, block, 0, s, ws, o, tile_lo,          \
