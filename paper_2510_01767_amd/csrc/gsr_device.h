@@ -154,8 +154,10 @@ struct Proj {
 // more inside the grid.  Both sides of the comparisons are multiplied by z, so
 // there is no division and no square root.  kIn also needs the 2D covariance
 // to be certainly positive definite in float64: a dilation of 0.01 or more
-// under a footprint of at most 1e4 pixels (its determinant then exceeds its
-// rounding by 1e5), and `sane` parameters.  An infinite or undefined bound
+// under a footprint of at most 1e4 pixels at one standard deviation or more
+// (its determinant then exceeds its rounding by 1e5; the bound counts the
+// footprint's own number of deviations, which may be a small fraction), and
+// `sane` parameters.  An infinite or undefined bound
 // leaves the decision to the exact test.
 enum Cull { kOut, kMaybe, kIn };
 
@@ -171,7 +173,8 @@ __device__ __forceinline__ Cull cull_view(const double mu[3], double smax, bool 
   const double rz = __fma_rn(k.reach_z, tz, rs);
   // (short circuits: a wavefront's neighbours in storage mostly leave at the same test)
   if (ax + rz < 0.0 || ay + rz < 0.0 || ax - rz > wz || ay - rz > hz) return kOut;
-  if (ACCEPT && sane && o.eps2d >= 0.01f && rs <= 1.0e4 * tz && ax >= tz && ay >= tz && ax <= wz - tz && ay <= hz - tz)
+  if (ACCEPT && sane && o.eps2d >= 0.01f && rs <= 1.0e4 * (double)fminf(o.sigma, 1.0f) * tz && ax >= tz && ay >= tz &&
+      ax <= wz - tz && ay <= hz - tz)
     return kIn;
   return kMaybe;
 }
