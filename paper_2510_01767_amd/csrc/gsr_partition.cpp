@@ -139,12 +139,14 @@ struct Selector {
     }
     for (int64_t k = 0; k < m; k++)
       if (const int w = number[cells[k]]) values[(size_t)w - 1].push_back(a[k]);
-    for (size_t r = 0; r < idx.size(); r++) {
-      std::vector<float> &v = values[of_rank[r]];
-      const int c = (int)(std::upper_bound(before.begin(), before.end(), idx[r]) - before.begin()) - 1;
-      const int64_t k = idx[r] - before[(size_t)c];
-      std::nth_element(v.begin(), v.begin() + k, v.end());
-      out[r] = v[(size_t)k];
+    // (a cell's ranks together: values that crowd into one cell, as in a box
+    // stretched by outliers, take one recursive selection, not one per rank)
+    std::vector<int64_t> local(idx.size());
+    for (size_t r0 = 0, r1; r0 < idx.size(); r0 = r1) {
+      std::vector<float> &v = values[of_rank[r0]];
+      const int64_t below = *(std::upper_bound(before.begin(), before.end(), idx[r0]) - 1);
+      for (r1 = r0; r1 < idx.size() && of_rank[r1] == of_rank[r0]; r1++) local[r1] = idx[r1] - below;
+      order_stats(v, 0, (int64_t)v.size(), local, r0, r1, out);
     }
   }
 };
