@@ -39,7 +39,7 @@ struct ViewTable {
 };
 
 // One view's camera in float64, with the per-view constants of the
-// projection and of the cull (cull_visible); made by the set-up kernel.
+// projection and of the cull (cull_view); made by the set-up kernel.
 struct Cam64 {
   double R[9], t[3], fx, fy, cx, cy;
   double limx, limy;  // clamp of x/z and y/z inside the Jacobian

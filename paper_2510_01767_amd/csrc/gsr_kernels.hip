@@ -219,7 +219,7 @@ __global__ __launch_bounds__(kBlock) void k_project(KParams p, KOpts o, KWs ws, 
         const float x = (float)(cam.R[0] * g.mu[0] + cam.R[1] * g.mu[1] + cam.R[2] * g.mu[2] + cam.t[0]);
         const float y = (float)(cam.R[3] * g.mu[0] + cam.R[4] * g.mu[1] + cam.R[5] * g.mu[2] + cam.t[1]);
         seen = z > o.near_plane;
-        // (clamped to 2^20 tiles; a NaN counts as 0)
+        // (clamped to 2^20 tiles either way; a NaN counts as -2^20)
         tx = (int)fminf(fmaxf((float)(cam.fx * cam.itw) * (x / z), -1048576.0f), 1048576.0f);
         ty = (int)fminf(fmaxf((float)(cam.fy * cam.ith) * (y / z), -1048576.0f), 1048576.0f);
       }

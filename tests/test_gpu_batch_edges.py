@@ -1,7 +1,7 @@
 """Raster batches hold one entry less than their size, the last place fills up
-the shorter sub-block lists, and the reverse pass reads the sub-block bits that
-the forward pass kept: one step and its gradients against the oracle with list
-lengths around the batch sizes, in every tile shape, batch size and reverse
+the shorter sub-block lists, and the reverse pass culls its batches anew (the
+fused one keeps the forward's last): one step and its gradients against the
+oracle with list lengths around the batch sizes, in every tile shape, batch size and reverse
 reduction, on images of few and of many tiles."""
 import numpy as np
 import pytest
